@@ -338,7 +338,8 @@ enum {
   CF_K_R2C_X = 0,     /* forward real transform along x (+ fused producers) */
   CF_K_FFT_Z_FWD = 1, /* forward complex transform along z */
   CF_K_YSOLVE = 2,    /* PDD wall-normal line solve */
-  CF_K_SPECIAL = 3,   /* whole-line FP64 Thomas (kx=kz=0 and the FP64 set) */
+  CF_K_SPECIAL = 3,   /* whole-line FP64 Thomas (kx=kz=0 and the FP64 set) next to the slab
+                          passes; the one-pass solve takes these lines in its CF_K_YSOLVE launch */
   CF_K_FFT_Z_INV = 4, /* inverse complex transform along z */
   CF_K_C2R_X = 5,     /* inverse real transform along x (+ fused consumers) */
   CF_K_DIVERGENCE = 6,

@@ -85,6 +85,25 @@ template <typename T>
 hipError_t launch_c2r_plain(int nh, const cx<T>* spec, double* p, const cx<T>* tw, const cx<T>* twp,
                             int ny, int nz, T scale, hipStream_t s);
 
+// Lines solved by whole-line FP64 Thomas: n line indices (kx*nz + kz) of layout
+// B and, per line and row ([n][ny]), the eliminated coefficients of its sweeps:
+// alpha = -a / den, rden = 1 / den, cp = c / den (den = b - a cp of the row
+// below).  psum (nullable): [ny][nzb] block sums of a pressure p; when given,
+// the kx = kz = 0 line is gauged to the dy-weighted mean -mean_W(p) * nx * nz
+// instead of 0, so that adding the solution to p makes mean_W vanish.  numflag
+// (nullable): set to 1 when that line of the input holds a non-finite value.
+struct SpecialLines {
+  const int* lines;
+  int n;
+  const double *alpha, *rden, *cp, *dy;
+  const double* psum;
+  int nzb;
+  int* numflag;
+};
+// Partial sums of a special line, and the LDS bytes of its solve.
+constexpr int kSpecialRed = 256;
+constexpr size_t special_lds_bytes(int ny) { return sizeof(double) * (5 * (size_t)ny + kSpecialRed); }
+
 struct YLaunch {
   int ny, nz, nkx, P, M;
   int LB;  // lines per block (threads per block = LB * P <= 512)
@@ -100,6 +119,8 @@ struct YLaunch {
   long n_exact = 0;
   const int* blocks_drop = nullptr;
   long n_drop = 0;
+  // whole mode: the special lines, solved by extra blocks of the (first) launch
+  SpecialLines special{};
 };
 
 // Default lines per block of the partitioned solve for P partitions.
@@ -111,16 +132,9 @@ template <typename T>
 hipError_t launch_ysolve(const YLaunch& y, const cx<T>* fin, cx<T>* pout, const T* a, const T* c,
                          const T* kx2, const T* kz2, hipStream_t s);
 
-// Whole-line FP64 Thomas on the listed lines of layout B, with per-line
-// elimination factors den, cp ([n_lines][ny]) prepared by the plan.  psum
-// (nullable): [ny][nzb] block sums of a pressure p; when given, the kx = kz = 0
-// line is gauged to the dy-weighted mean -mean_W(p) * nx * nz instead of 0, so
-// that adding the solution to p makes mean_W vanish.  numflag (nullable): set
-// to 1 when the kx = kz = 0 line of fin holds a non-finite value.
+// Whole-line FP64 Thomas on the special lines alone (next to the slab passes).
 template <typename T>
-hipError_t launch_special_lines(const cx<T>* fin, cx<T>* pout, const double* a, const double* den,
-                                const double* cp, const double* dy, const int* lines, int n_lines,
-                                int ny, int nz, const double* psum, int nzb, int* numflag, hipStream_t s);
+hipError_t launch_special_lines(const cx<T>* fin, cx<T>* pout, const SpecialLines& sp, int ny, int nz, hipStream_t s);
 
 bool ysolve_m_compiled(int m, bool fp64);
 

@@ -131,8 +131,8 @@ struct cf_plan {
   double* d_lamy = nullptr;
   cx<float>*tw_z32 = nullptr, *tw_x32 = nullptr, *twp32 = nullptr;
   int* d_special = nullptr;
-  double* d_special_den = nullptr;  // [n_special][ny] elimination pivots
-  double* d_special_cp = nullptr;   // [n_special][ny] eliminated upper coefficients
+  // [n_special][ny]: -a / den, 1 / den and c / den of the lines' eliminations
+  double *d_special_alpha = nullptr, *d_special_rden = nullptr, *d_special_cp = nullptr;
   // spectral workspaces of the bulk precision: layout A (ny, nkx, nz) on the
   // x side, layout B (nkx, ny, nz) on the wall-normal side
   void* specA = nullptr;
@@ -533,11 +533,21 @@ cf_status inverse_t(cf_plan* pl, const cx<T>* inB, double* p, hipStream_t s) {
   return CF_OK;
 }
 
+// The plan's special lines; psum (nullable): block sums of the pressure a
+// correction solve adds to.
+cf::SpecialLines special_lines(const cf_plan* pl, const double* psum = nullptr) {
+  return cf::SpecialLines{pl->d_special,      (int)pl->special.size(), pl->d_special_alpha,
+                          pl->d_special_rden, pl->d_special_cp,        pl->d_dy,
+                          psum,               psum ? pl->psum_nzb : 0, pl->d_numflag};
+}
+
 // One launch of the partitioned line solve with the plan's partitioning (whole
-// lines, or one slab's local or finishing pass over partitions [pa, pb)).
+// lines, with the special lines given, or one slab's local or finishing pass
+// over partitions [pa, pb)).
 template <typename T>
-hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStream_t s, int mode = cf::kWhole,
-                      int pa = 0, int pb = 0, void* iface = nullptr) {
+hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStream_t s,
+                      const cf::SpecialLines& special = cf::SpecialLines{}, int mode = cf::kWhole, int pa = 0,
+                      int pb = 0, void* iface = nullptr) {
   using TB = Tabs<T>;
   cf::YLaunch y;
   y.ny = pl->ny;
@@ -554,6 +564,7 @@ hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStrea
   y.pb = pb;
   y.iface = iface;
   y.G = pl->G;
+  y.special = special;
   if (pl->d_blocks) {
     y.blocks_exact = pl->d_blocks;
     y.n_exact = (long)pl->blocks_exact.size();
@@ -572,26 +583,23 @@ cf_status slabs_t(cf_plan* pl, int n_slabs, const cx<T>* fin, cx<T>* pout, void*
   const int per = pl->P / n_slabs;
   for (int g = 0; g < n_slabs; ++g)
     CF_TRY(timed(pl, CF_K_SLAB_LOCAL, s, "slab local launch", [&] {
-      return pdd_launch<T>(pl, fin, pout, s, cf::kSlabLocal, g * per, (g + 1) * per, iface);
+      return pdd_launch<T>(pl, fin, pout, s, {}, cf::kSlabLocal, g * per, (g + 1) * per, iface);
     }));
   CF_HIP(hipEventRecord(pl->ev_fork, s), "hipEventRecord");
   CF_HIP(hipStreamWaitEvent(pl->aux, pl->ev_fork, 0), "hipStreamWaitEvent");
   CF_TRY(timed(pl, CF_K_SPECIAL, pl->aux, "special-line launch", [&] {
-    return cf::launch_special_lines<T>(fin, pout, pl->d_a, pl->d_special_den, pl->d_special_cp, pl->d_dy,
-                                       pl->d_special, (int)pl->special.size(), pl->ny, pl->nz, nullptr, 0,
-                                       pl->d_numflag, pl->aux);
+    return cf::launch_special_lines<T>(fin, pout, special_lines(pl), pl->ny, pl->nz, pl->aux);
   }));
   CF_HIP(hipEventRecord(pl->ev_join, pl->aux), "hipEventRecord");
   for (int g = 0; g < n_slabs; ++g)
     CF_TRY(timed(pl, CF_K_SLAB_FINISH, s, "slab finish launch", [&] {
-      return pdd_launch<T>(pl, fin, pout, s, cf::kSlabFinish, g * per, (g + 1) * per, iface);
+      return pdd_launch<T>(pl, fin, pout, s, {}, cf::kSlabFinish, g * per, (g + 1) * per, iface);
     }));
   CF_HIP(hipStreamWaitEvent(s, pl->ev_join, 0), "hipStreamWaitEvent");
   return CF_OK;
 }
 
-// psum (nullable): block sums of the pressure a correction solve adds to (see
-// launch_special_lines).
+// psum (nullable): block sums of the pressure a correction solve adds to.
 template <typename T>
 cf_status solve_t(cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStream_t s, const double* psum = nullptr) {
   if constexpr (std::is_same<T, double>::value) {
@@ -601,23 +609,11 @@ cf_status solve_t(cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStream_t s, con
                                        pl->nz, pl->nkx, s);
       });
   }
-  // The whole-line solves run on the side stream next to the PDD kernel: they
-  // read and write only the special lines, which the PDD kernel reads but does
-  // not write (lines are independent there, so the values it reads for them
-  // are discarded).
-  CF_HIP(hipEventRecord(pl->ev_fork, s), "hipEventRecord");
-  CF_HIP(hipStreamWaitEvent(pl->aux, pl->ev_fork, 0), "hipStreamWaitEvent");
-  CF_TRY(timed(pl, CF_K_SPECIAL, pl->aux, "special-line launch", [&] {
-    return cf::launch_special_lines<T>(fin, pout, pl->d_a, pl->d_special_den, pl->d_special_cp, pl->d_dy,
-                                       pl->d_special, (int)pl->special.size(), pl->ny, pl->nz, psum,
-                                       psum ? pl->psum_nzb : 0, pl->d_numflag, pl->aux);
-  }));
-  CF_HIP(hipEventRecord(pl->ev_join, pl->aux), "hipEventRecord");
-  CF_TRY(timed(pl, CF_K_YSOLVE, s, "y-solve launch", [&] {
-    return pdd_launch<T>(pl, fin, pout, s);
-  }));
-  CF_HIP(hipStreamWaitEvent(s, pl->ev_join, 0), "hipStreamWaitEvent");
-  return CF_OK;
+  // The whole-line solves are blocks of the same launch: they read and write
+  // only the special lines, which the PDD blocks read but do not write (lines
+  // are independent there, so the values read for them are discarded).
+  return timed(pl, CF_K_YSOLVE, s, "y-solve launch",
+               [&] { return pdd_launch<T>(pl, fin, pout, s, special_lines(pl, psum)); });
 }
 
 template <typename T>
@@ -823,28 +819,24 @@ cf_status step_adjoint_t(cf_plan* pl, const T* u, const T* v, const T* w, const 
   return CF_OK;
 }
 
-// Elimination factors of one whole-line solve, in the operation order of the
-// textbook Thomas algorithm (no contraction).
-void special_factors(const cf_plan* pl, int line, double* den, double* cp) {
-#pragma clang fp contract(off)
+// Elimination factors of one whole-line solve (Thomas), in the solved form of
+// its sweeps: alpha = -a / den, rden = 1 / den, cp = c / den.
+void special_factors(const cf_plan* pl, int line, double* alpha, double* rden, double* cp) {
   const int ny = pl->ny, nz = pl->nz;
   const int kx = line / nz, kz = line % nz;
   const double k2 = pl->kx2[kx] + pl->kz2[kz];
-  const bool mean_line = (line == 0);
-  const int n = mean_line ? ny - 1 : ny;
+  const int n = line == 0 ? ny - 1 : ny;  // the k^2 = 0 line leaves its top row out
   double cprev = 0.0;
   for (int j = 0; j < ny; ++j) {
     if (j >= n) {
-      den[j] = 1.0;
-      cp[j] = 0.0;
+      alpha[j] = cp[j] = 0.0;
+      rden[j] = 1.0;
       continue;
     }
-    const double b = -(pl->a[j] + pl->c[j]) - k2;
-    const double t = pl->a[j] * cprev;
-    const double d = (j == 0) ? b : b - t;
-    const double cj = (j == n - 1) ? 0.0 : pl->c[j];
-    den[j] = d;
-    cp[j] = cj / d;
+    const double den = -(pl->a[j] + pl->c[j]) - k2 - pl->a[j] * cprev;
+    alpha[j] = -pl->a[j] / den;
+    rden[j] = 1.0 / den;
+    cp[j] = (j == n - 1) ? 0.0 : pl->c[j] / den;
     cprev = cp[j];
   }
 }
@@ -1201,10 +1193,11 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
   if ((st = upload_blocks(pl)) != CF_OK) return bail(st);
   if ((st = upload(pl, &pl->d_special, pl->special)) != CF_OK) return bail(st);
   {
-    std::vector<double> den(pl->special.size() * (size_t)ny), cpv(den.size());
+    std::vector<double> al(pl->special.size() * (size_t)ny), rd(al.size()), cpv(al.size());
     for (size_t l = 0; l < pl->special.size(); ++l)
-      special_factors(pl, pl->special[l], den.data() + l * ny, cpv.data() + l * ny);
-    if ((st = upload(pl, &pl->d_special_den, den)) != CF_OK) return bail(st);
+      special_factors(pl, pl->special[l], al.data() + l * ny, rd.data() + l * ny, cpv.data() + l * ny);
+    if ((st = upload(pl, &pl->d_special_alpha, al)) != CF_OK) return bail(st);
+    if ((st = upload(pl, &pl->d_special_rden, rd)) != CF_OK) return bail(st);
     if ((st = upload(pl, &pl->d_special_cp, cpv)) != CF_OK) return bail(st);
   }
   if (tune && (st = tune_partitions(pl, (size_t)lds_max)) != CF_OK) return bail(st);

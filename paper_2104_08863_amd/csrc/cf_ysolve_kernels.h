@@ -18,11 +18,12 @@
 // (YMode) split this kernel at the interface exchange: the interface rows go
 // through a global buffer instead of LDS.
 //
-// k_special_lines: FP64 Thomas along whole lines, one block per line, with
-// the gauge handling of the singular kx = kz = 0 line and its check for
-// non-finite values.
+// special_line: FP64 Thomas along a whole line by one block, with the gauge
+// handling of the singular kx = kz = 0 line and its check for non-finite
+// values; these lines are the first blocks of the one-pass solve's launch.
 #pragma once
 
+#include "cf_internal.h"
 #include "cf_pdd.h"
 
 namespace cf {
@@ -58,6 +59,159 @@ __host__ __device__ constexpr size_t ysolve_lds_bytes(int nyp, int P, int LB, bo
          (sizeof(cx<T>) * 4 + sizeof(T) * 4 + (drop ? sizeof(zrow3<T>) : sizeof(zrow<T>))) * size_t(P) * LB;
 }
 
+// FP64 Thomas on one whole line by one block of any size.  The plan gives the
+// line's elimination in solved form: row j of the forward sweep is x_j =
+// al_j x_{j-1} + f_j rd_j (al_j = -a_j / den_j, rd_j = 1 / den_j), row j of the
+// backward sweep x_j -= cp_j x_{j+1}, so a row of either sweep is one fused
+// multiply-add; threads 0 and 1 run the two chains of the real and the
+// imaginary part (the division form of the same sweeps took 18 us on a line of
+// 64 rows and 65 us on one of 256, which nothing hides on a small grid; this
+// one is part of the partitioned solve's launch and ends with it).  The k^2 = 0
+// line, solved with its top row left out, is made compatible first (dy-weighted
+// mean of the right-hand side removed) and shifted afterwards to zero
+// dy-weighted mean (or, for a correction solve given the block sums psum of the
+// pressure it corrects, to -sum_j dy_j sum(p_j) / sum_j dy_j, the line value of
+// the constant -mean_W(p)).  All sums are taken in an order that does not
+// depend on the block size.  Reads of fin precede writes of pout, which may
+// alias.  sm: special_lds_bytes(ny) bytes.
+template <typename T>
+__device__ __forceinline__ void special_line(const SpecialLines& sp, int l, const cx<T>* fin, cx<T>* pout, int ny,
+                                             int nz, double* sm) {
+  double* fr = sm;
+  double* fi = fr + ny;
+  double* sa = fi + ny;
+  double* sd = sa + ny;
+  double* sc = sd + ny;
+  double* red = sc + ny;  // kSpecialRed doubles
+  const long line = sp.lines[l];
+  const int kx = int(line / nz), kz = int(line % nz);
+  const long base = (long)kx * ny * nz + kz;
+  const bool mean_line = (kx == 0 && kz == 0);
+  const int tid = threadIdx.x, nt = blockDim.x;
+  for (int j = tid; j < ny; j += nt) {
+    const cx<T> f = fin[base + (long)j * nz];
+    const double rd = sp.rden[(long)l * ny + j];
+    sa[j] = sp.alpha[(long)l * ny + j];
+    sc[j] = sp.cp[(long)l * ny + j];
+    sd[j] = mean_line ? rd : sp.dy[j];
+    fr[j] = mean_line ? double(f.re) : double(f.re) * rd;
+    fi[j] = mean_line ? double(f.im) : double(f.im) * rd;
+  }
+  __syncthreads();
+  // A non-finite value anywhere in a plane of the right-hand side reaches that
+  // plane's row of the kx = kz = 0 line (the sum over the plane): flag it for
+  // cf_plan_numeric_status.
+  if (mean_line && sp.numflag) {
+    bool bad = false;
+    for (int j = tid; j < ny; j += nt) bad = bad || !__builtin_isfinite(fr[j]) || !__builtin_isfinite(fi[j]);
+    if (bad) *sp.numflag = 1;
+  }
+  // tree sums of `groups` runs of `width` partial sums in red
+  auto tree = [&](int groups, int width) {
+    for (int h = width / 2; h > 0; h /= 2) {
+      __syncthreads();
+      for (int e = tid; e < groups * h; e += nt) red[(e / h) * width + e % h] += red[(e / h) * width + h + e % h];
+    }
+    __syncthreads();
+  };
+  // dy-weighted means of the line, used by the k^2 = 0 line only
+  auto wmean = [&](double& mr, double& mi) {
+    for (int q = tid; q < 64; q += nt) {
+      double r = 0.0, im = 0.0, w = 0.0;
+      for (int j = q; j < ny; j += 64) {
+        const double d = sp.dy[j];
+        r += d * fr[j];
+        im += d * fi[j];
+        w += d;
+      }
+      red[q] = r;
+      red[64 + q] = im;
+      red[128 + q] = w;
+    }
+    tree(3, 64);
+    mr = red[0] / red[128];
+    mi = red[64] / red[128];
+    __syncthreads();
+  };
+  if (mean_line) {
+    double mr, mi;
+    wmean(mr, mi);
+    for (int j = tid; j < ny; j += nt) {
+      fr[j] = (fr[j] - mr) * sd[j];
+      fi[j] = (fi[j] - mi) * sd[j];
+    }
+    __syncthreads();
+  }
+  const int n = mean_line ? ny - 1 : ny;
+  for (int part = tid; part < 2; part += nt) {
+    double* x = part == 0 ? fr : fi;
+    // sweeps in chunks of C rows; a chunk's operands are read while the chain
+    // of the chunk before runs
+    constexpr int C = 8;
+    double al[C], be[C], na[C], nb[C];
+    double xj = x[0];
+    auto fetch = [&](const double* t, int j0, int dir, double* a_, double* b_) {
+#pragma unroll
+      for (int u = 0; u < C; ++u) {
+        const int j = min(max(j0 + dir * u, 0), n - 1);
+        a_[u] = t[j];
+        b_[u] = x[j];
+      }
+    };
+    fetch(sa, 1, 1, al, be);
+    for (int j0 = 1; j0 < n; j0 += C) {
+      fetch(sa, j0 + C, 1, na, nb);
+#pragma unroll
+      for (int u = 0; u < C; ++u)
+        if (j0 + u < n) {
+          xj = __builtin_fma(al[u], xj, be[u]);
+          x[j0 + u] = xj;
+        }
+#pragma unroll
+      for (int u = 0; u < C; ++u) al[u] = na[u], be[u] = nb[u];
+    }
+    fetch(sc, n - 2, -1, al, be);
+    for (int j0 = n - 2; j0 >= 0; j0 -= C) {
+      fetch(sc, j0 - C, -1, na, nb);
+#pragma unroll
+      for (int u = 0; u < C; ++u)
+        if (j0 - u >= 0) {
+          xj = __builtin_fma(-al[u], xj, be[u]);
+          x[j0 - u] = xj;
+        }
+#pragma unroll
+      for (int u = 0; u < C; ++u) al[u] = na[u], be[u] = nb[u];
+    }
+    if (mean_line) x[ny - 1] = 0.0;
+  }
+  __syncthreads();
+  double orr = 0.0, oi = 0.0;
+  if (mean_line) wmean(orr, oi);
+  if (mean_line && sp.psum) {
+    // sum_j dy_j sum_b psum[j][b] / sum_j dy_j (the weights' sum is in red[128])
+    const double wsum = red[128];
+    __syncthreads();
+    for (int q = tid; q < kSpecialRed; q += nt) {
+      double s = 0.0;
+#pragma unroll 8
+      for (int e = q; e < ny * sp.nzb; e += kSpecialRed) s += sp.dy[e / sp.nzb] * sp.psum[e];
+      red[q] = s;
+    }
+    tree(1, kSpecialRed);
+    orr += red[0] / wsum;
+  }
+  for (int j = tid; j < ny; j += nt) pout[base + (long)j * nz] = mk(T(fr[j] - orr), T(fi[j] - oi));
+}
+
+// The special lines alone, one block each (next to the y-slab passes; the
+// one-pass solve's launch takes them in as its first blocks).
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_special_lines(const cx<T>* fin, cx<T>* pout, SpecialLines sp, int ny, int nz) {
+  extern __shared__ __align__(16) double special_sm[];
+  special_line<T>(sp, blockIdx.x, fin, pout, ny, nz, special_sm);
+}
+
 // DROP: every line of the block lies above the plan's k^2 threshold (the
 // launch covers only such blocks) and the reduced system takes the dropped
 // form; otherwise it is solved exactly.  blist (nullable): the blocks of the
@@ -80,8 +234,17 @@ template <typename T, int M, int MODE, bool DROP, bool NT = false>
 __global__ void __launch_bounds__(512, sizeof(T) != 4 ? 1 : M == 24 ? 4 : M == 32 ? 3 : 1)
 k_ysolve(const cx<T>* fin, cx<T>* pout, const T* __restrict__ acoef,
          const T* __restrict__ ccoef, const T* __restrict__ kx2, const T* __restrict__ kz2,
-         const int* __restrict__ blist, YArgs ya) {
+         const int* __restrict__ blist, YArgs ya, SpecialLines sp) {
   extern __shared__ __align__(16) unsigned char smem[];
+  if constexpr (MODE == kWhole) {
+    // The first sp.n blocks solve the special lines; the others read those
+    // lines too (and discard what they read), so neither waits for the other.
+    if ((int)blockIdx.x < sp.n) {
+      special_line<T>(sp, blockIdx.x, fin, pout, ya.ny, ya.nz, reinterpret_cast<double*>(smem));
+      return;
+    }
+  }
+  const int bid = (int)blockIdx.x - (MODE == kWhole ? sp.n : 0);
   const int LB = ya.LB, P = ya.P, ny = ya.ny, nyp = P * M;
   T* sa = reinterpret_cast<T*>(smem);
   T* sc = sa + nyp;
@@ -103,7 +266,7 @@ k_ysolve(const cx<T>* fin, cx<T>* pout, const T* __restrict__ acoef,
   // partition of this thread (a local-mode block has threads for [pa, pb) only)
   const int i = threadIdx.x / LB + (MODE == kSlabLocal ? ya.pa : 0);
   const bool own = (MODE == kWhole) || (i >= ya.pa && i < ya.pb);
-  const long blk = blist ? (long)blist[blockIdx.x] : (long)blockIdx.x;
+  const long blk = blist ? (long)blist[bid] : (long)bid;
   const long line = blk * LB + q;
   const bool ok = line < ya.nlines;
   const int kx = ok ? int(line / ya.nz) : 0;
@@ -291,167 +454,6 @@ k_ysolve(const cx<T>* fin, cx<T>* pout, const T* __restrict__ acoef,
     for (int s = 0; s < M; ++s)
       if (j0 + s < ny) st_once<NT>(d[s], &pout[base + s * rs]);
   }
-}
-
-// FP64 Thomas on whole lines, one block per line.  The elimination factors
-// of each listed line (den_j = b_j - a_j cp_{j-1}, cp_j = c_j / den_j, with the
-// top row left out for the k^2 = 0 line) come from the plan.  The k^2 = 0
-// line is made compatible (dy-weighted mean of the RHS removed), solved with
-// its top unknown pinned to zero, and shifted to zero dy-weighted mean (or,
-// for a correction solve given the block sums psum of the pressure it
-// corrects, to the weighted mean -sum_j dy_j sum(p_j) / sum_j dy_j, the line
-// value of the constant -mean_W(p)).  The
-// line is staged in LDS; reads of fin all precede writes of pout, so the two
-// may alias.  The sweeps follow the textbook operation order without
-// contraction, like the reference definition.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_special_lines(const cx<T>* fin, cx<T>* pout, const double* __restrict__ a,
-                const double* __restrict__ den, const double* __restrict__ cpt,
-                const double* __restrict__ dy, const int* __restrict__ lines, int ny, int nz,
-                const double* __restrict__ psum, int nzb, int* __restrict__ numflag) {
-#pragma clang fp contract(off)
-  extern __shared__ __align__(16) double sm[];
-  double* fr = sm;
-  double* fi = fr + ny;
-  double* sa = fi + ny;
-  double* sd = sa + ny;
-  double* sc = sd + ny;
-  double* red = sc + ny;  // 3 * blockDim doubles
-  const int l = blockIdx.x;
-  const long line = lines[l];
-  const int kx = int(line / nz), kz = int(line % nz);
-  const long base = (long)kx * ny * nz + kz;
-  const bool mean_line = (kx == 0 && kz == 0);
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (int j = tid; j < ny; j += nt) {
-    const cx<T> f = fin[base + (long)j * nz];
-    fr[j] = double(f.re);
-    fi[j] = double(f.im);
-    sa[j] = a[j];
-    sd[j] = den[(long)l * ny + j];
-    sc[j] = cpt[(long)l * ny + j];
-  }
-  __syncthreads();
-  // A non-finite value anywhere in a plane of the right-hand side reaches that
-  // plane's row of the kx = kz = 0 line (the sum over the plane): flag it for
-  // cf_plan_numeric_status.
-  if (mean_line && numflag) {
-    bool bad = false;
-    for (int j = tid; j < ny; j += nt) bad = bad || !__builtin_isfinite(fr[j]) || !__builtin_isfinite(fi[j]);
-    if (bad) *numflag = 1;
-  }
-  // dy-weighted means (block reduction), used by the k^2 = 0 line only
-  auto wmean = [&](double& mr, double& mi) {
-    double r = 0.0, im = 0.0, w = 0.0;
-    for (int j = tid; j < ny; j += nt) {
-      r += dy[j] * fr[j];
-      im += dy[j] * fi[j];
-      w += dy[j];
-    }
-    red[tid] = r;
-    red[nt + tid] = im;
-    red[2 * nt + tid] = w;
-    __syncthreads();
-    for (int h = nt / 2; h > 0; h /= 2) {
-      if (tid < h) {
-        red[tid] += red[tid + h];
-        red[nt + tid] += red[nt + tid + h];
-        red[2 * nt + tid] += red[2 * nt + tid + h];
-      }
-      __syncthreads();
-    }
-    mr = red[0] / red[2 * nt];
-    mi = red[nt] / red[2 * nt];
-    __syncthreads();
-  };
-  if (mean_line) {
-    double mr, mi;
-    wmean(mr, mi);
-    for (int j = tid; j < ny; j += nt) {
-      fr[j] = fr[j] - mr;
-      fi[j] = fi[j] - mi;
-    }
-    __syncthreads();
-  }
-  const int n = mean_line ? ny - 1 : ny;
-  if (tid == 0) {
-    // sweeps in chunks of 8 rows whose operands are read before the chain
-    constexpr int C = 8;
-    double xr = fr[0] / sd[0], xi = fi[0] / sd[0];
-    fr[0] = xr;
-    fi[0] = xi;
-    for (int j0 = 1; j0 < n; j0 += C) {
-      double ar[C], br[C], bi[C], dr[C];
-#pragma unroll
-      for (int u = 0; u < C; ++u) {
-        const int j = j0 + u < n ? j0 + u : n - 1;
-        ar[u] = sa[j];
-        br[u] = fr[j];
-        bi[u] = fi[j];
-        dr[u] = sd[j];
-      }
-#pragma unroll
-      for (int u = 0; u < C; ++u) {
-        if (j0 + u < n) {
-          const double tr = ar[u] * xr, ti = ar[u] * xi;
-          xr = (br[u] - tr) / dr[u];
-          xi = (bi[u] - ti) / dr[u];
-          fr[j0 + u] = xr;
-          fi[j0 + u] = xi;
-        }
-      }
-    }
-    for (int j0 = n - 2; j0 >= 0; j0 -= C) {
-      double cr[C], br[C], bi[C];
-#pragma unroll
-      for (int u = 0; u < C; ++u) {
-        const int j = j0 - u >= 0 ? j0 - u : 0;
-        cr[u] = sc[j];
-        br[u] = fr[j];
-        bi[u] = fi[j];
-      }
-#pragma unroll
-      for (int u = 0; u < C; ++u) {
-        if (j0 - u >= 0) {
-          const double tr = cr[u] * xr, ti = cr[u] * xi;
-          xr = br[u] - tr;
-          xi = bi[u] - ti;
-          fr[j0 - u] = xr;
-          fi[j0 - u] = xi;
-        }
-      }
-    }
-    if (mean_line) {
-      fr[ny - 1] = 0.0;
-      fi[ny - 1] = 0.0;
-    }
-  }
-  __syncthreads();
-  double orr = 0.0, oi = 0.0;
-  if (mean_line) wmean(orr, oi);
-  if (mean_line && psum) {
-    // -sum_j dy_j sum_b psum[j][b] / sum_j dy_j, summed in a fixed order
-    double sp = 0.0, w = 0.0;
-    for (int j = tid; j < ny; j += nt) {
-      double rowsum = 0.0;
-      for (int b = 0; b < nzb; ++b) rowsum += psum[(long)j * nzb + b];
-      sp += dy[j] * rowsum;
-      w += dy[j];
-    }
-    red[tid] = sp;
-    red[nt + tid] = w;
-    __syncthreads();
-    for (int h = nt / 2; h > 0; h /= 2) {
-      if (tid < h) {
-        red[tid] += red[tid + h];
-        red[nt + tid] += red[nt + tid + h];
-      }
-      __syncthreads();
-    }
-    orr += red[0] / red[nt];
-  }
-  for (int j = tid; j < ny; j += nt) pout[base + (long)j * nz] = mk(T(fr[j] - orr), T(fi[j] - oi));
 }
 
 }  // namespace cf

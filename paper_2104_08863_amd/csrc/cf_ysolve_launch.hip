@@ -41,21 +41,24 @@ int ysolve_default_lb(int P, int M) {
 
 template <typename T, int M, int MODE, bool DROP>
 static hipError_t ysolve_go(long blocks, const int* blist, const YArgs& ya, int threads, const cx<T>* fin,
-                            cx<T>* pout, const T* a, const T* c, const T* kx2, const T* kz2, hipStream_t s) {
+                            cx<T>* pout, const T* a, const T* c, const T* kx2, const T* kz2, hipStream_t s,
+                            const SpecialLines& sp = SpecialLines{}) {
+  blocks += sp.n;
   if (blocks <= 0) return hipSuccess;
   const int nyp = ya.P * M;  // rows of the partitions (padded past ny)
-  const size_t lds = MODE == kSlabLocal ? sizeof(T) * 2 * (size_t)nyp : ysolve_lds_bytes<T>(nyp, ya.P, ya.LB, DROP);
+  size_t lds = MODE == kSlabLocal ? sizeof(T) * 2 * (size_t)nyp : ysolve_lds_bytes<T>(nyp, ya.P, ya.LB, DROP);
+  if (sp.n > 0 && lds < special_lds_bytes(ya.ny)) lds = special_lds_bytes(ya.ny);
   if constexpr (MODE == kWhole) {
     // the slab passes read their right-hand side twice: only the one-pass
     // solve streams it
     if ((long)ya.nlines * ya.ny * (long)sizeof(cx<T>) >= kStreamBytes) {
       hipLaunchKernelGGL((k_ysolve<T, M, MODE, DROP, true>), dim3(blocks), dim3(threads), lds, s, fin, pout, a, c,
-                         kx2, kz2, blist, ya);
+                         kx2, kz2, blist, ya, sp);
       return hipGetLastError();
     }
   }
   hipLaunchKernelGGL((k_ysolve<T, M, MODE, DROP, false>), dim3(blocks), dim3(threads), lds, s, fin, pout, a, c, kx2,
-                     kz2, blist, ya);
+                     kz2, blist, ya, sp);
   return hipGetLastError();
 }
 
@@ -75,9 +78,15 @@ static hipError_t ysolve_m(const YLaunch& y, const YArgs& ya, int threads, const
     if (e == hipSuccess && y.blocks_drop)
       e = ysolve_go<T, M, kSlabFinish, true>(y.n_drop, y.blocks_drop, ya, threads, fin, pout, a, c, kx2, kz2, s);
   } else {
-    e = ysolve_go<T, M, kWhole, false>(ne, y.blocks_exact, ya, threads, fin, pout, a, c, kx2, kz2, s);
+    // the special lines go with the first launch: the exact blocks, or the
+    // dropped ones when every block drops
+    const bool with_exact = ne > 0 || !y.blocks_drop;
+    const SpecialLines none{};
+    e = ysolve_go<T, M, kWhole, false>(ne, y.blocks_exact, ya, threads, fin, pout, a, c, kx2, kz2, s,
+                                       with_exact ? y.special : none);
     if (e == hipSuccess && y.blocks_drop)
-      e = ysolve_go<T, M, kWhole, true>(y.n_drop, y.blocks_drop, ya, threads, fin, pout, a, c, kx2, kz2, s);
+      e = ysolve_go<T, M, kWhole, true>(y.n_drop, y.blocks_drop, ya, threads, fin, pout, a, c, kx2, kz2, s,
+                                        with_exact ? none : y.special);
   }
   return e;
 }
@@ -139,23 +148,16 @@ size_t ysolve_lds_needed(int nyp, int P, int LB, bool fp64) {
 }
 
 template <typename T>
-hipError_t launch_special_lines(const cx<T>* fin, cx<T>* pout, const double* a, const double* den,
-                                const double* cp, const double* dy, const int* lines, int n_lines,
-                                int ny, int nz, const double* psum, int nzb, int* numflag, hipStream_t s) {
-  if (n_lines <= 0) return hipSuccess;
-  const int th = 256;
-  const size_t lds = sizeof(double) * (5 * (size_t)ny + 3 * th);
-  hipLaunchKernelGGL((k_special_lines<T>), dim3(n_lines), dim3(th), lds, s, fin, pout, a, den, cp, dy, lines,
-                     ny, nz, psum, nzb, numflag);
+hipError_t launch_special_lines(const cx<T>* fin, cx<T>* pout, const SpecialLines& sp, int ny, int nz, hipStream_t s) {
+  if (sp.n <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_special_lines<T>), dim3(sp.n), dim3(256), special_lds_bytes(ny), s, fin, pout, sp, ny, nz);
   return hipGetLastError();
 }
 
 #define CF_INST(T)                                                                                  \
   template hipError_t launch_ysolve<T>(const YLaunch&, const cx<T>*, cx<T>*, const T*, const T*,   \
                                        const T*, const T*, hipStream_t);                           \
-  template hipError_t launch_special_lines<T>(const cx<T>*, cx<T>*, const double*, const double*, \
-                                              const double*, const double*, const int*, int, int, int, \
-                                              const double*, int, int*, hipStream_t);
+  template hipError_t launch_special_lines<T>(const cx<T>*, cx<T>*, const SpecialLines&, int, int, hipStream_t);
 CF_INST(double)
 CF_INST(float)
 #undef CF_INST
