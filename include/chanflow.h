@@ -63,7 +63,10 @@ typedef struct {
                          divide ny the last partition is padded with decoupled rows */
   double drop_tol;    /* lines whose PDD corner terms are all <= drop_tol use the dropped
                          (2x2) reduced system; the others the exact one.  < 0 = default
-                         (1e-15 FP64, 1e-7 mixed) */
+                         (1e-15 FP64, 1e-7 mixed).  At the default or below it the two
+                         systems agree to the round-off of the precision, and the solve
+                         takes the exact one, which is faster on one device, for every
+                         line */
   int fp64_kx;        /* CF_MIXED: lines with kx < fp64_kx and min(kz, nz-kz) < fp64_kz */
   int fp64_kz;        /*   are solved in FP64 (default 4, 4) */
   int refine_passes;  /* CF_MIXED: FP64 residual + correction solves (default 1; one pass
@@ -111,9 +114,10 @@ typedef struct {
   size_t slab_iface_bytes; /* device bytes of the interface buffer of cf_solve_spectral_slabs:
                               n_parts * 8 * n_lines values of the plan's precision */
   int drop_parts;         /* G, the outer partitions of the dropped reduced system */
-  long long n_dropped_lines; /* lines the partitioned solve drops the corner terms for: those
-                              whose block of lines_per_block consecutive lines lies wholly
-                              above k2_threshold (the others take the exact reduced system) */
+  long long n_dropped_lines; /* lines whose block of lines_per_block consecutive lines lies
+                              wholly above k2_threshold: those the partitioned solve may drop
+                              the corner terms for, and does when drop_tol is above its
+                              default (the others take the exact reduced system) */
 } cf_plan_info;
 
 /* Fill *opt with the defaults. */
@@ -125,10 +129,11 @@ void cf_options_default(cf_options* opt);
  * nx, nz: even, 2^a or 3*2^a, nx/2 and nz in [2, 2048] (nz >= 2).
  * ny >= 2, split into P <= 64 partitions of M = ceil(ny/P) rows with M in
  * {1,2,3,4,6,8,12,16} (CF_MIXED: also 24, 32) and (P-1)*M < ny: any ny up to
- * 1024 (CF_MIXED: 2048).  The automatic P is the fewest partitions that divide
- * ny, preferring powers of two, else the partitioning with the fewest padding
- * rows (the rows P*M - ny that complete the last partition: no-flux rows below
- * the top wall row, decoupled from the line).
+ * 1024 (CF_MIXED: 2048).  When P does not divide ny, P*M - ny padding rows
+ * complete the last partition (no-flux rows below the top wall row, decoupled
+ * from the line).  The automatic P: a power of two that divides ny, or in CF_FP64
+ * the count whose rows and reduced system cost least, padding included, and in
+ * CF_MIXED the fewest partitions that divide ny, else the fewest padding rows.
  * y_faces: host, ny+1 strictly increasing finite values (walls at both ends).
  * opt: NULL for defaults.  On success *out receives the plan; on failure *out is
  * set to NULL and nothing is leaked.

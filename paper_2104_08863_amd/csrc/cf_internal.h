@@ -100,6 +100,8 @@ struct SpecialLines {
   int nzb;
   int* numflag;
 };
+// Blocks the special lines take at the head of a launch: a multiple of the 8 XCDs.
+constexpr CF_HD int special_blocks(int n) { return (n + 7) / 8 * 8; }
 // Partial sums of a special line, and the LDS bytes of its solve.
 constexpr int kSpecialRed = 256;
 constexpr size_t special_lds_bytes(int ny) { return sizeof(double) * (5 * (size_t)ny + kSpecialRed); }
@@ -123,8 +125,8 @@ struct YLaunch {
   SpecialLines special{};
 };
 
-// Default lines per block of the partitioned solve for P partitions.
-int ysolve_default_lb(int P, int M);
+// Default lines per block of the partitioned solve for P partitions of M rows.
+int ysolve_default_lb(int P, int M, bool fp64);
 // Dynamic LDS of one partitioned-solve block.
 size_t ysolve_lds_needed(int nyp, int P, int LB, bool fp64);
 

@@ -107,6 +107,10 @@ struct cf_plan {
   // then the dropped one)
   std::vector<int> blocks_exact, blocks_drop;
   int* d_blocks = nullptr;
+  // drop_tol is at the round-off of the precision: the exact and the dropped
+  // reduced system then give the same solution, and every block takes the
+  // exact one, which is the faster kernel on one device
+  bool exact_all = false;
   // partition counts and block shapes timed at creation (CF_PLAN_TUNE_PARTS)
   struct TuneRow {
     int P, LB;
@@ -399,18 +403,36 @@ bool parts_ok(int ny, int P, bool fp64) {
   return cf::ysolve_m_compiled(M, fp64) && (P - 1) * M < ny;
 }
 
+// Automatic partition count.  FP64: the least rows * (1 + 16/M) over the
+// admissible P, rows = P*M: a partition costs its rows plus, for its share of
+// the reduced system, about as much as 16 rows (the order of the timings of
+// every admissible P on 36 ny from 24 to 768, within 8 % of the fastest; the
+// fewest padding rows alone, down to one- and two-row partitions, took 277
+// instead of 54 us on 512x97x256 and 373 instead of 171 us on 512x341x256); a
+// power of two that divides ny keeps its place within 20 % of that, which the
+// timings do not tell apart (192 rows: 16 x 12 81 us, 12 x 16 83 us).  CF_MIXED:
+// the fewest partitions that divide ny, preferring powers of two, else the
+// fewest padding rows (another count rounds the FP32 solve differently).
 int auto_parts(int ny, bool fp64) {
-  // fewest partitions with a compiled row count (at most 16 rows in FP64, 32 in
-  // FP32) that divide ny, preferring powers of two; if none divides ny, the
-  // partitioning with the fewest padding rows (then the fewest partitions)
-  for (int P = 1; P <= 64; P *= 2)
-    if (ny % P == 0 && parts_ok(ny, P, fp64)) return P;
-  for (int P = 1; P <= 64; ++P)
-    if (ny % P == 0 && parts_ok(ny, P, fp64)) return P;
+  auto cost = [ny](int P) {
+    const int M = part_rows(ny, P);
+    return double(P * M) * (1.0 + 16.0 / M);
+  };
+  int pow2 = 0;
+  for (int P = 1; P <= 64 && pow2 == 0; P *= 2)
+    if (ny % P == 0 && parts_ok(ny, P, fp64)) pow2 = P;
+  if (!fp64) {
+    if (pow2) return pow2;
+    for (int P = 1; P <= 64; ++P)
+      if (ny % P == 0 && parts_ok(ny, P, fp64)) return P;
+  }
   int best = 0;
-  for (int P = 1; P <= 64; ++P)
-    if (parts_ok(ny, P, fp64) && (best == 0 || P * part_rows(ny, P) < best * part_rows(ny, best))) best = P;
-  return best;
+  for (int P = 1; P <= 64; ++P) {
+    if (!parts_ok(ny, P, fp64)) continue;
+    const bool less = best == 0 || (fp64 ? cost(P) < cost(best) : P * part_rows(ny, P) < best * part_rows(ny, best));
+    if (less) best = P;
+  }
+  return pow2 && cost(pow2) <= 1.2 * cost(best) ? pow2 : best;
 }
 
 cf_status check_plan(const cf_plan* pl) {
@@ -565,7 +587,7 @@ hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStrea
   y.iface = iface;
   y.G = pl->G;
   y.special = special;
-  if (pl->d_blocks) {
+  if (pl->d_blocks && !pl->exact_all) {
     y.blocks_exact = pl->d_blocks;
     y.n_exact = (long)pl->blocks_exact.size();
     y.blocks_drop = pl->blocks_drop.empty() ? nullptr : pl->d_blocks + pl->blocks_exact.size();
@@ -965,12 +987,13 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     return fail(CF_ERR_ARG, "lines_per_block must be >= 0 with lines_per_block * n_parts <= 512");
   if (opt.drop_parts < 0 || (opt.drop_parts > 0 && (tune || P % opt.drop_parts != 0)))
     return fail(CF_ERR_ARG, "drop_parts must be 0 or divide n_parts (and be 0 with CF_PLAN_TUNE_PARTS)");
-  const int LB = opt.lines_per_block > 0 ? opt.lines_per_block : cf::ysolve_default_lb(P, part_rows(ny, P));
+  const int LB = opt.lines_per_block > 0 ? opt.lines_per_block : cf::ysolve_default_lb(P, part_rows(ny, P), fp64);
   if (opt.precision == CF_MIXED) {
     if (opt.fp64_kx < 1 || opt.fp64_kz < 1) return fail(CF_ERR_ARG, "fp64_kx and fp64_kz must be >= 1");
     if (opt.refine_passes < 0 || opt.refine_passes > 8) return fail(CF_ERR_ARG, "refine_passes must be in [0, 8]");
   }
-  if (opt.drop_tol < 0) opt.drop_tol = (opt.precision == CF_MIXED) ? 1e-7 : 1e-15;
+  const double round_off = (opt.precision == CF_MIXED) ? 1e-7 : 1e-15;
+  if (opt.drop_tol < 0) opt.drop_tol = round_off;
   if (opt.flags & CF_PLAN_Y_DCT) {
     if (opt.precision != CF_FP64) return fail(CF_ERR_UNSUPPORTED, "the y-transform solve is FP64 only");
     if (ny % 2 != 0 || !cf::ydct_len_compiled(ny))
@@ -992,6 +1015,7 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
   pl->dx = lx / nx;
   pl->dz = lz / nz;
   pl->opt = opt;
+  pl->exact_all = opt.drop_tol <= round_off;
   pl->P = P;
   pl->M = part_rows(ny, P);
   pl->yf.assign(y_faces, y_faces + ny + 1);

@@ -236,15 +236,16 @@ k_ysolve(const cx<T>* fin, cx<T>* pout, const T* __restrict__ acoef,
          const T* __restrict__ ccoef, const T* __restrict__ kx2, const T* __restrict__ kz2,
          const int* __restrict__ blist, YArgs ya, SpecialLines sp) {
   extern __shared__ __align__(16) unsigned char smem[];
+  const int nsp = MODE == kWhole ? special_blocks(sp.n) : 0;
   if constexpr (MODE == kWhole) {
     // The first sp.n blocks solve the special lines; the others read those
     // lines too (and discard what they read), so neither waits for the other.
-    if ((int)blockIdx.x < sp.n) {
-      special_line<T>(sp, blockIdx.x, fin, pout, ya.ny, ya.nz, reinterpret_cast<double*>(smem));
+    if ((int)blockIdx.x < nsp) {
+      if ((int)blockIdx.x < sp.n) special_line<T>(sp, blockIdx.x, fin, pout, ya.ny, ya.nz, reinterpret_cast<double*>(smem));
       return;
     }
   }
-  const int bid = (int)blockIdx.x - (MODE == kWhole ? sp.n : 0);
+  const int bid = (int)blockIdx.x - nsp;
   const int LB = ya.LB, P = ya.P, ny = ya.ny, nyp = P * M;
   T* sa = reinterpret_cast<T*>(smem);
   T* sc = sa + nyp;

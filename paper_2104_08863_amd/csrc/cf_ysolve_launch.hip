@@ -22,19 +22,28 @@ bool ysolve_m_compiled(int m, bool fp64) {
   }
 }
 
-// Default lines per block: about 256 threads per block with 8 to 16 lines (to
-// 32 for the FP32-only partitions of more than 16 rows), and at least one
-// wave.  Those FP32 partitions take at least 16 lines, so that each row of a
-// block is a 128-byte run of consecutive lines, up to 512 threads.  Measured
-// on MI355X for the default partitionings of the workload grids this is the
-// fastest block or within 2 % of it (P = 32 partitions of 24 rows on
-// 2048x768x2048: 7.0 ms per launch at 16 lines against 7.4 at 8); other shapes
-// can be chosen by measurement.
-int ysolve_default_lb(int P, int M) {
-  const int hi = M > 16 ? 32 : 16;
-  int lb = 256 / P;
-  if (M > 16 && lb < 16) lb = 16 * P <= 512 ? 16 : 512 / P;
-  lb = lb < 8 ? 8 : (lb > hi ? hi : lb);
+// Default lines per block, from timings of every admissible partitioning of
+// 512 x ny x 256 with 24 <= ny <= 768.  A row access of a block should be whole
+// 128-byte lines, 8 FP64 or 16 FP32 values.
+//   FP64: at most 256 threads (two blocks per CU at 192 VGPRs; 288 threads of 18
+//     partitions are 20-30 % slower than 216), and of those the most lines in
+//     multiples of 8 (9 x 16 rows: 59 us at 24 lines, 65 at 28, 69 at 16), or 12
+//     lines where 16 do not fit (19 x 16 rows: 143 us at 12 lines, 165 at 8; at
+//     13 lines, which 256 threads would take, 255).
+//   FP32: 16 lines (25 x 12 rows: 104 us, 204 at 10; 13 x 24 rows: 72 us, 167 at
+//     19), 32 where at most 8 partitions leave the block small, and for 16
+//     partitions of 24 rows (1024x384x1024: 574 us, 659 at 16).
+// At least one wave and, above 32 partitions, what 512 threads hold.
+int ysolve_default_lb(int P, int M, bool fp64) {
+  int lb;
+  if (fp64) {
+    lb = 256 / P;
+    lb = lb >= 16 ? lb & ~7 : (lb >= 12 ? 12 : 8);
+    if (lb > 48) lb = 48;
+  } else {
+    lb = P <= 8 || (P == 16 && M == 24) ? 32 : 16;
+  }
+  if (lb * P > 512) lb = P <= 64 ? 8 : 512 / P;
   if (lb * P < 64) lb = (64 + P - 1) / P;
   return lb;
 }
@@ -43,7 +52,7 @@ template <typename T, int M, int MODE, bool DROP>
 static hipError_t ysolve_go(long blocks, const int* blist, const YArgs& ya, int threads, const cx<T>* fin,
                             cx<T>* pout, const T* a, const T* c, const T* kx2, const T* kz2, hipStream_t s,
                             const SpecialLines& sp = SpecialLines{}) {
-  blocks += sp.n;
+  blocks += special_blocks(sp.n);
   if (blocks <= 0) return hipSuccess;
   const int nyp = ya.P * M;  // rows of the partitions (padded past ny)
   size_t lds = MODE == kSlabLocal ? sizeof(T) * 2 * (size_t)nyp : ysolve_lds_bytes<T>(nyp, ya.P, ya.LB, DROP);
@@ -99,7 +108,7 @@ hipError_t launch_ysolve(const YLaunch& y, const cx<T>* fin, cx<T>* pout, const 
   ya.nz = y.nz;
   ya.nkx = y.nkx;
   ya.P = y.P;
-  ya.LB = y.LB > 0 ? y.LB : ysolve_default_lb(y.P, y.M);
+  ya.LB = y.LB > 0 ? y.LB : ysolve_default_lb(y.P, y.M, std::is_same<T, double>::value);
   ya.nlines = y.nlines;
   ya.skip_kx = y.skip_kx;
   ya.skip_kz = y.skip_kz;
