@@ -197,7 +197,7 @@ struct AdjPtrs {
 };
 
 // out = s * J_R(state)^T lam (+ A + B when ADD), lam = c1 A (+ c2 B when HASB).
-// 2.5D tiling as in k_rk_stage: a TX x TZ column tile marches over CY planes
+// 2.5D tiling as in k_rk_stage: a TX x TZ column tile marches over cy planes
 // keeping three planes of the six fields in LDS, the raw values of plane j+2
 // fetched into registers while plane j is computed.  lam is formed only when a
 // plane moves from registers to LDS, and every global load is unconditional
@@ -211,15 +211,16 @@ struct AdjPtrs {
 // of 82.8 on 2048x768x2048 in FP32, 5.7 instead of 6.5 on 1024x256x512 in FP64.
 // NT: outputs, written once, stored non-temporally for large fields (the
 // two launches of an FP32 adjoint step on 2048x768x2048: 72-74 -> 71.5 ms).
-template <typename T, int TX, int TZ, int CY, bool HASB, bool ADD, bool NT>
-__global__ void __launch_bounds__(TX * TZ)
-k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s) {
+// FP64: three waves per SIMD (168 VGPRs), the most the LDS of its blocks lets run.
+template <typename T, int TX, int TZ, bool HASB, bool ADD, bool NT>
+__global__ void __launch_bounds__(TX * TZ, sizeof(T) == 8 ? 3 : 1)
+k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {
   constexpr int SX = TX + 2, SZ = TZ + 2, PLANE = SX * SZ, TH = TX * TZ;
   constexpr int NHALO = PLANE - TH;                // 2 SX + 2 TZ ring cells
   constexpr int PER = 1 + (NHALO + TH - 1) / TH;  // own cell first, then ring cells
   constexpr int NF = HASB ? 9 : 6;  // raw fields fetched per tile value
   __shared__ T sm[6 * 3 * PLANE];
-  __shared__ T sy[4 * (CY + 2)];
+  __shared__ T sy[4 * (kMaxChunk + 2)];
   const T* src[9] = {static_cast<const T*>(P.u),  static_cast<const T*>(P.v),  static_cast<const T*>(P.w),
                      static_cast<const T*>(P.au), static_cast<const T*>(P.av), static_cast<const T*>(P.aw),
                      static_cast<const T*>(P.bu), static_cast<const T*>(P.bv), static_cast<const T*>(P.bw)};
@@ -232,7 +233,7 @@ k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s) {
   const int bz = b % ntz;
   const int by = b / ntz;
   const int i0 = bx * TX, k0 = bz * TZ;
-  const int j0 = by * CY, j1 = (j0 + CY < ny) ? j0 + CY : ny;
+  const int j0 = by * cy, j1 = (j0 + cy < ny) ? j0 + cy : ny;
   const int tx = threadIdx.x % TX, tz = threadIdx.x / TX;
   const int i = i0 + tx, k = k0 + tz;
   const bool mine = (i < nx) && (k < nz);
@@ -311,7 +312,7 @@ k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s) {
   T* gu = static_cast<T*>(P.gu);
   T* gv = static_cast<T*>(P.gv);
   T* gw = static_cast<T*>(P.gw);
-  const YTab<T> Y = ytab_fill(sy, CY + 2, j0 - 1, g);
+  const YTab<T> Y = ytab_fill(sy, kMaxChunk + 2, j0 - 1, g);
   AdjCarry<T> carry{T(0), T(0), T(0)};
   bool have = false;
   for (int j = j0; j < j1; ++j) {

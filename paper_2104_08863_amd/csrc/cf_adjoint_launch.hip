@@ -5,20 +5,19 @@
 namespace cf {
 
 // Tile of the transposed stencil (six LDS fields x three planes) and chunks of
-// 32 planes.  FP64: 32 x 8 columns (51 KB of LDS, three blocks per CU; 64 x 8
+// at most 32 planes.  FP64: 32 x 8 columns (51 KB of LDS, three blocks per CU; 64 x 8
 // and 32 x 16 were slower, 32-plane chunks 2 % faster than 64 and 16).  FP32:
 // 64 x 8 columns, 36 % faster than 32 x 8 and ahead of 64 x 16, 128 x 4,
 // 128 x 8 and 32 x 16 on 512x384x512 (half the LDS per value lets the wider
 // tile keep its occupancy while cutting the halo share).
 template <typename T>
 struct AdjTile {
-  static constexpr int TX = 32, TZ = 8;
+  static constexpr int TX = 32, TZ = 8, BPC = 3;
 };
 template <>
 struct AdjTile<float> {
-  static constexpr int TX = 64, TZ = 8;
+  static constexpr int TX = 64, TZ = 8, BPC = 3;
 };
-constexpr int ADJ_CY = 32;
 
 template <typename T>
 hipError_t launch_rhs_adjoint(const T* u, const T* v, const T* w, const T* au, const T* av, const T* aw,
@@ -26,17 +25,18 @@ hipError_t launch_rhs_adjoint(const T* u, const T* v, const T* w, const T* au, c
                               int add, T* gu, T* gv, T* gw, hipStream_t st) {
   constexpr int ADJ_TX = AdjTile<T>::TX, ADJ_TZ = AdjTile<T>::TZ;
   AdjPtrs P{u, v, w, au, av, aw, bu, bv, bw, gu, gv, gw};
-  const long blocks = (long)((g.g.nx + ADJ_TX - 1) / ADJ_TX) * ((g.g.nz + ADJ_TZ - 1) / ADJ_TZ) *
-                      ((g.g.ny + ADJ_CY - 1) / ADJ_CY);
+  const long cols = (long)((g.g.nx + ADJ_TX - 1) / ADJ_TX) * ((g.g.nz + ADJ_TZ - 1) / ADJ_TZ);
+  const int cy = chunk_planes(cols, g.g.ny, AdjTile<T>::BPC * kCus, kMaxChunk, 2);
+  const long blocks = cols * ((g.g.ny + cy - 1) / cy);
   const dim3 grid(blocks), block(ADJ_TX * ADJ_TZ);
   const bool nt = (long)g.g.nx * g.g.ny * g.g.nz * (long)sizeof(T) >= kStreamBytes;
 #define CF_ADJ_GO(HASB, ADD)                                                                                     \
   if (nt)                                                                                                        \
-    hipLaunchKernelGGL((k_rhs_adjoint<T, ADJ_TX, ADJ_TZ, ADJ_CY, HASB, ADD, true>), grid, block, 0, st, P, c1, c2, \
-                       g, nu, s);                                                                                \
+    hipLaunchKernelGGL((k_rhs_adjoint<T, ADJ_TX, ADJ_TZ, HASB, ADD, true>), grid, block, 0, st, P, c1, c2, g, nu, \
+                       s, cy);                                                                                \
   else                                                                                                           \
-    hipLaunchKernelGGL((k_rhs_adjoint<T, ADJ_TX, ADJ_TZ, ADJ_CY, HASB, ADD, false>), grid, block, 0, st, P, c1,   \
-                       c2, g, nu, s)
+    hipLaunchKernelGGL((k_rhs_adjoint<T, ADJ_TX, ADJ_TZ, HASB, ADD, false>), grid, block, 0, st, P, c1, c2, g, nu, \
+                       s, cy)
   if (bu != nullptr && add) {
     CF_ADJ_GO(true, true);
   } else if (bu != nullptr) {

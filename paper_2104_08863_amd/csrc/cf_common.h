@@ -106,6 +106,9 @@ __device__ __forceinline__ void st_once(cx<T> v, cx<T>* a) {
 // 64^3 time loop was 2-4 % slower).
 constexpr long kStreamBytes = 32L << 20;
 
+// Compute units of the chip (8 XCDs of 32).
+constexpr int kCus = 256;
+
 // Work order for the 8 XCDs, each with its own L2.  The hardware deals
 // blocks round-robin (block b to XCD b mod 8); for a grid made of groups of n
 // consecutive work items (n a multiple of 8), block b is given the item that

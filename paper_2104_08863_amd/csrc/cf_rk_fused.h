@@ -91,6 +91,9 @@ __device__ __forceinline__ void rk_stage1_point(const T* su, const T* sv, const 
   bw[boff] = ow;
 }
 
+// Most planes of one y-chunk (the metric rows of a chunk are staged in LDS).
+constexpr int kRkfMaxChunk = 128;
+
 template <int TX, int TZ>
 struct RkFusedTile {
   static constexpr int TH = TX * TZ;
@@ -107,16 +110,17 @@ struct RkFusedTile {
 // lines in one L2 (runs within each y-chunk instead: within 1.5 %, either way).
 // NT: the outputs, written once, are streamed (non-temporal) for large fields
 // (the FP64 pass on 1024x256x512: about 2 % faster).
-template <typename T, int TX, int TZ, int CY, bool NT>
+// cy: planes of a block's chunk, at most kRkfMaxChunk (see chunk_planes).
+template <typename T, int TX, int TZ, bool NT>
 __global__ void __launch_bounds__(TX * TZ, 4)
 k_rk2_fused(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w, T* uo, T* vo, T* wo,
-            Geo<T> g, T dt, T nu, T fx) {
+            Geo<T> g, T dt, T nu, T fx, int cy) {
   using Tl = RkFusedTile<TX, TZ>;
   constexpr int TH = Tl::TH, EX = Tl::EX, EPL = Tl::EPL, UX = Tl::UX, UPL = Tl::UPL, PER = Tl::PER;
   static_assert(Tl::NRING <= TH, "the grown tile's outer cells must fit one pass of the block");
   __shared__ T su[2 * UPL], sv[2 * UPL], sw[2 * UPL];
   __shared__ T bu[3 * EPL], bv[3 * EPL], bw[3 * EPL];
-  __shared__ T sy[4 * (CY + 4)];
+  __shared__ T sy[4 * (kRkfMaxChunk + 4)];
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const int ntx = (nx + TX - 1) / TX, ntz = (nz + TZ - 1) / TZ;
   int b = xcd_slab_block(blockIdx.x, gridDim.x);
@@ -125,7 +129,7 @@ k_rk2_fused(const T* __restrict__ u, const T* __restrict__ v, const T* __restric
   const int bz = b % ntz;
   const int by = b / ntz;
   const int i0 = bx * TX, k0 = bz * TZ;
-  const int j0 = by * CY, j1 = (j0 + CY < ny) ? j0 + CY : ny;
+  const int j0 = by * cy, j1 = (j0 + cy < ny) ? j0 + cy : ny;
   const int t = threadIdx.x;
   const int tx = t % TX, tz = t / TX;
   const int i = i0 + tx, k = k0 + tz;
@@ -185,7 +189,7 @@ k_rk2_fused(const T* __restrict__ u, const T* __restrict__ v, const T* __restric
   CF_RKF_STORE(j0 - 2)
   CF_RKF_FETCH(j0 - 1)
   CF_RKF_STORE(j0 - 1)
-  const YTab<T> Y = ytab_fill(sy, CY + 4, j0 - 2, g);
+  const YTab<T> Y = ytab_fill(sy, kRkfMaxChunk + 4, j0 - 2, g);
   __syncthreads();
   // stage-1 carries at face j0-1 and the columns at plane j0-2
   ColState<T> sA, sB;

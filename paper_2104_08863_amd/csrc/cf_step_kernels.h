@@ -150,13 +150,32 @@ __device__ __forceinline__ RhsOut<T> momentum_rhs(const Acc& A, const Geo<T>& g,
 }
 
 // 2.5D tiling: a block owns TX x TZ columns (x, z) and marches over a chunk of
-// CY planes in y, keeping three consecutive planes of u, v, w (with a one-cell
+// cy planes in y, keeping three consecutive planes of u, v, w (with a one-cell
 // halo in x and z, periodic wrap) in LDS; every field value is read from
 // global memory once per plane step plus the halo.
-template <int TX, int TZ, int CY>
+template <int TX, int TZ>
 struct RkTile {
   static constexpr int SX = TX + 2, SZ = TZ + 2, PLANE = SX * SZ, THREADS = TX * TZ;
 };
+// Most planes of one y-chunk of the split stages and the transposed stencil.
+constexpr int kMaxChunk = 32;
+
+// Planes per y-chunk of a marching kernel: `cols` column tiles, `slots` blocks
+// on the chip at a time, `extra` plane times a chunk spends before its first
+// plane.  The longest chunk within 4 % of the least rounds * (planes + extra): a
+// grid of few columns is cut until its blocks fill the chip once, and one of many
+// keeps long chunks (there the blocks do not run in rounds: FP64 split stages on
+// 1024x256x512 in 29 instead of 32 planes, 0.5 % less by this count, are 4 %
+// slower).
+inline int chunk_planes(long cols, int ny, long slots, int max_planes, int extra) {
+  const int top = max_planes < ny ? max_planes : ny;
+  auto cost = [&](int cy) { return (cols * ((ny + cy - 1) / cy) + slots - 1) / slots * (cy + extra); };
+  long least = cost(top);
+  for (int cy = top - 1; cy >= 1; --cy) least = cost(cy) < least ? cost(cy) : least;
+  for (int cy = top; cy > 1; --cy)
+    if (100 * cost(cy) <= 104 * least) return cy;
+  return 1;
+}
 
 template <typename T, int TX, int TZ>
 struct LdsAcc {
@@ -180,14 +199,14 @@ struct LdsAcc {
 // the FP32 stage on 2048x768x2048 runs in 17.2 ms instead of 22.0.
 // NT: outputs, written once, stored non-temporally for large fields (FP64
 // stage 1 on 1024x256x512: 1.37-1.43 -> 1.30 ms).
-template <typename T, int STAGE, int TX, int TZ, int CY, bool NT>
+template <typename T, int STAGE, int TX, int TZ, bool NT>
 __global__ void __launch_bounds__(TX * TZ)
 k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
-           const T* u0, const T* v0, const T* w0, T* uo, T* vo, T* wo, Geo<T> g, T dt, T nu, T fx) {
-  using Tl = RkTile<TX, TZ, CY>;
+           const T* u0, const T* v0, const T* w0, T* uo, T* vo, T* wo, Geo<T> g, T dt, T nu, T fx, int cy) {
+  using Tl = RkTile<TX, TZ>;
   constexpr int PER = (Tl::PLANE + Tl::THREADS - 1) / Tl::THREADS;  // tile values per thread
   __shared__ T su[3 * Tl::PLANE], sv[3 * Tl::PLANE], sw[3 * Tl::PLANE];
-  __shared__ T sy[4 * (CY + 2)];
+  __shared__ T sy[4 * (kMaxChunk + 2)];
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const int ntx = (nx + TX - 1) / TX, ntz = (nz + TZ - 1) / TZ;
   int b = xcd_slab_block(blockIdx.x, ntx * ntz);
@@ -196,7 +215,7 @@ k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict
   const int bz = b % ntz;
   const int by = b / ntz;
   const int i0 = bx * TX, k0 = bz * TZ;
-  const int j0 = by * CY, j1 = (j0 + CY < ny) ? j0 + CY : ny;
+  const int j0 = by * cy, j1 = (j0 + cy < ny) ? j0 + cy : ny;
   const int tx = threadIdx.x % TX, tz = threadIdx.x / TX;
   const int i = i0 + tx, k = k0 + tz;
   const bool mine = (i < nx) && (k < nz);
@@ -246,7 +265,7 @@ k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict
     c0 = w0[(long)j0 * plane + pid];
   }
   LdsAcc<T, TX, TZ> A{su, sv, sw, 0, 0, 0, (tz + 1) * Tl::SX + tx + 1};
-  const YTab<T> Y = ytab_fill(sy, CY + 2, j0 - 1, g);
+  const YTab<T> Y = ytab_fill(sy, kMaxChunk + 2, j0 - 1, g);
   FaceFlux<T> carry{T(0), T(0)};
   bool have = false;
   for (int j = j0; j < j1; ++j) {

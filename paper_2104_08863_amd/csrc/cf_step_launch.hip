@@ -6,20 +6,22 @@
 
 namespace cf {
 
-// Split-stage tile: 64 x 8 columns, chunks of 32 planes.
-constexpr int RK_TX = 64, RK_TZ = 8, RK_CY = 32;
+// Split-stage tile: 64 x 8 columns, chunks of at most 32 planes, three blocks
+// per CU (FP64 LDS).
+constexpr int RK_TX = 64, RK_TZ = 8, RK_BPC = 3;
 
 template <typename T>
 hipError_t launch_rk_stage(int stage, const T* u, const T* v, const T* w, const T* u0, const T* v0,
                            const T* w0, T* uo, T* vo, T* wo, const Geo<T>& g, T dt, T nu, T fx,
                            hipStream_t s) {
-  const long blocks = (long)((g.nx + RK_TX - 1) / RK_TX) * ((g.nz + RK_TZ - 1) / RK_TZ) *
-                      ((g.ny + RK_CY - 1) / RK_CY);
+  const long cols = (long)((g.nx + RK_TX - 1) / RK_TX) * ((g.nz + RK_TZ - 1) / RK_TZ);
+  const int cy = chunk_planes(cols, g.ny, RK_BPC * kCus, kMaxChunk, 2);
+  const long blocks = cols * ((g.ny + cy - 1) / cy);
   const dim3 th(RK_TX * RK_TZ);
   const bool nt = (long)g.nx * g.ny * g.nz * (long)sizeof(T) >= kStreamBytes;
 #define CF_RK_GO(ST, NT)                                                                                         \
-  hipLaunchKernelGGL((k_rk_stage<T, ST, RK_TX, RK_TZ, RK_CY, NT>), dim3(blocks), th, 0, s, u, v, w, u0, v0, w0, \
-                     uo, vo, wo, g, dt, nu, fx)
+  hipLaunchKernelGGL((k_rk_stage<T, ST, RK_TX, RK_TZ, NT>), dim3(blocks), th, 0, s, u, v, w, u0, v0, w0, uo, vo, \
+                     wo, g, dt, nu, fx, cy)
   if (stage == 1) {
     if (nt) CF_RK_GO(1, true);
     else CF_RK_GO(1, false);
@@ -33,41 +35,35 @@ hipError_t launch_rk_stage(int stage, const T* u, const T* v, const T* w, const 
 
 // Fused RK2 tile.  FP64: 64 x 16 columns, one block of 16 waves per CU (stage 1
 // on the 66 x 18 grown tile, whose 164 outer cells keep 3 of the 16 waves busy
-// for one more stencil pass).  FP32: 64 x 8 columns, two blocks per CU (half
+// for one more stencil pass).  FP32: 64 x 8 columns, three blocks per CU (half
 // the LDS per value; 6 % faster than 64 x 16 on a 512x384x512 mixed step,
-// 64 x 4 was 15 % slower).  Chunks of 128 planes; shorter chunks (32, then 8
-// planes) when that leaves fewer than two blocks per CU, as on small grids.
+// 64 x 4 was 15 % slower).  Chunks of at most 128 planes, cut so that the blocks
+// come out in full rounds over the chip: a chunk spends about four plane times
+// before its first plane.  Against chunks of 128, 32 or 8 planes alone: FP64
+// 384x97x192 189 -> 137 us, 64^3 40 -> 16 us, FP32 512x192x512 664 -> 513 us.
 template <typename T>
 struct RkfTile {
-  static constexpr int TX = 64, TZ = 16;
+  static constexpr int TX = 64, TZ = 16, BPC = 1;
 };
 template <>
 struct RkfTile<float> {
-  static constexpr int TX = 64, TZ = 8;
+  static constexpr int TX = 64, TZ = 8, BPC = 3;
 };
 
 template <typename T>
 hipError_t launch_rk2_fused(const T* u, const T* v, const T* w, T* uo, T* vo, T* wo, const Geo<T>& g, T dt, T nu,
                             T fx, hipStream_t s) {
-  constexpr int RKF_TX = RkfTile<T>::TX, RKF_TZ = RkfTile<T>::TZ;
-  const long cols = (long)((g.nx + RKF_TX - 1) / RKF_TX) * ((g.nz + RKF_TZ - 1) / RKF_TZ);
-  auto blocks = [&](int cy) { return cols * ((g.ny + cy - 1) / cy); };
-  const dim3 th(RKF_TX * RKF_TZ);
-  const bool nt = (long)g.nx * g.ny * g.nz * (long)sizeof(T) >= kStreamBytes;
-#define CF_RKF_GO(CY, NT)                                                                                          \
-  hipLaunchKernelGGL((k_rk2_fused<T, RKF_TX, RKF_TZ, CY, NT>), dim3(blocks(CY)), th, 0, s, u, v, w, uo, vo, wo, g, \
-                     dt, nu, fx)
-  if (blocks(128) >= 512) {
-    if (nt) CF_RKF_GO(128, true);
-    else CF_RKF_GO(128, false);
-  } else if (blocks(32) >= 512) {
-    if (nt) CF_RKF_GO(32, true);
-    else CF_RKF_GO(32, false);
-  } else {
-    if (nt) CF_RKF_GO(8, true);
-    else CF_RKF_GO(8, false);
-  }
-#undef CF_RKF_GO
+  using Tl = RkfTile<T>;
+  const long cols = (long)((g.nx + Tl::TX - 1) / Tl::TX) * ((g.nz + Tl::TZ - 1) / Tl::TZ);
+  const int cy = chunk_planes(cols, g.ny, Tl::BPC * kCus, kRkfMaxChunk, 4);
+  const long blocks = cols * ((g.ny + cy - 1) / cy);
+  const dim3 th(Tl::TX * Tl::TZ);
+  if ((long)g.nx * g.ny * g.nz * (long)sizeof(T) >= kStreamBytes)
+    hipLaunchKernelGGL((k_rk2_fused<T, Tl::TX, Tl::TZ, true>), dim3(blocks), th, 0, s, u, v, w, uo, vo, wo, g, dt, nu,
+                       fx, cy);
+  else
+    hipLaunchKernelGGL((k_rk2_fused<T, Tl::TX, Tl::TZ, false>), dim3(blocks), th, 0, s, u, v, w, uo, vo, wo, g, dt,
+                       nu, fx, cy);
   return hipGetLastError();
 }
 
