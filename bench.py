@@ -76,7 +76,7 @@ def kernel_source_hash(kernel: str) -> str | None:
     for f in files:
         h.update(f.encode())
         h.update(open(os.path.join(B.CSRC, f), "rb").read())
-        flags = [a for a in B.HIP_FLAGS + B.EXTRA_FLAGS.get(f, []) if not a.startswith("/")]
+        flags = [a for a in B.HIP_FLAGS if not a.startswith("/")]
         h.update(" ".join(flags).encode())
     return h.hexdigest()
 

@@ -34,6 +34,38 @@ struct AdjGeo {
   const T* rdyc;  // 1/dyc
 };
 
+// The wall-normal metric rows a y-chunk touches (jb .. jb + n - 1 of 1/dy,
+// 1/dyc, wl and wu, zero where a table has no entry), staged in LDS once per
+// block, plus 1/dy of the two wall cells held in registers.  The marching
+// stencils read them from here so that no per-plane global load shares the
+// in-order vector-memory counter with the next plane's prefetch: a wait for
+// such a load would also wait for the prefetch and serialise the pipeline.
+template <typename T>
+struct YTab {
+  const T* s;  // 4 x n values in LDS
+  int n, jb;
+  T rdy_bot, rdy_top;
+  __device__ __forceinline__ T rdy(int j) const { return s[j - jb]; }
+  __device__ __forceinline__ T rdyc(int j) const { return s[n + j - jb]; }
+  __device__ __forceinline__ T wl(int j) const { return s[2 * n + j - jb]; }
+  __device__ __forceinline__ T wu(int j) const { return s[3 * n + j - jb]; }
+};
+
+// Block-cooperative fill of a YTab over rows jb .. jb + n - 1; the caller
+// synchronises before the first read.
+template <typename T>
+__device__ __forceinline__ YTab<T> ytab_fill(T* s, int n, int jb, const Geo<T>& g) {
+  for (int t = threadIdx.x; t < n; t += blockDim.x) {
+    const int jj = jb + t;
+    const bool in = jj >= 0 && jj < g.ny - 1;
+    s[t] = (jj >= 0 && jj < g.ny) ? g.rdy[jj] : T(0);
+    s[n + t] = in ? g.rdyc[jj] : T(0);
+    s[2 * n + t] = in ? g.wl[jj] : T(0);
+    s[3 * n + t] = in ? g.wu[jj] : T(0);
+  }
+  return YTab<T>{s, n, jb, g.rdy[0], g.rdy[g.ny - 1]};
+}
+
 // J_R(u)^T lam at point (i, j, k) from an accessor with relative offsets:
 // A.U(dj, dk, di) etc. for the state and A.LU(...) for lam; A returns 0 outside
 // [0, ny) and for v / lam_v on the top wall.

@@ -124,6 +124,8 @@ struct cf_plan {
   // device tables (FP64 and FP32 copies)
   double *d_a = nullptr, *d_c = nullptr, *d_dy = nullptr, *d_rdy = nullptr, *d_kx2 = nullptr,
          *d_kz2 = nullptr, *d_rdyc = nullptr, *d_wl = nullptr, *d_wu = nullptr;
+  double* d_rows = nullptr;  // momentum stencil factors by plane (YRow), padded
+  float* s_rows = nullptr;
   float *s_rdy = nullptr, *s_rdyc = nullptr, *s_wl = nullptr, *s_wu = nullptr;
   float *s_a = nullptr, *s_c = nullptr, *s_kx2 = nullptr, *s_kz2 = nullptr;
   cx<double>*tw_z64 = nullptr, *tw_x64 = nullptr, *twp64 = nullptr;
@@ -1149,9 +1151,25 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     if ((st = upload(pl, &pl->s_wl, tof(wl))) != CF_OK) return bail(st);
     if ((st = upload(pl, &pl->s_wu, tof(wu))) != CF_OK) return bail(st);
     const double rdx = 1.0 / pl->dx, rdz = 1.0 / pl->dz;
-    pl->g64 = cf::Geo<double>{pl->d_rdy, pl->d_rdyc, pl->d_wl, pl->d_wu, rdx, rdz, rdx * rdx, rdz * rdz, nx, ny, nz};
+    std::vector<double> rows((size_t)(ny + 2 * cf::kRowPad) * 8, 0.0);
+    for (int j = 0; j < ny; ++j) {
+      double* r = rows.data() + (size_t)(j + cf::kRowPad) * 8;
+      const bool top = j == ny - 1;
+      r[0] = rdy[j];
+      r[1] = top ? 0.0 : rdy[j + 1];
+      r[2] = top ? 0.0 : 0.5 * wl[j];
+      r[3] = top ? 0.0 : 0.5 * wu[j];
+      r[4] = j == 0 ? 2.0 * rdy[0] : rdyc[j - 1];
+      r[5] = top ? 2.0 * rdy[j] : rdyc[j];
+      r[6] = top ? 0.0 : 0.25 * rdyc[j];
+    }
+    if ((st = upload(pl, &pl->d_rows, rows)) != CF_OK) return bail(st);
+    if ((st = upload(pl, &pl->s_rows, tof(rows))) != CF_OK) return bail(st);
+    pl->g64 = cf::Geo<double>{pl->d_rdy, pl->d_rdyc, pl->d_wl, pl->d_wu, rdx, rdz, rdx * rdx, rdz * rdz,
+                              0.25 * rdx, 0.25 * rdz, nx, ny, nz, pl->d_rows + cf::kRowPad * 8};
     pl->g32 = cf::Geo<float>{pl->s_rdy, pl->s_rdyc, pl->s_wl, pl->s_wu, (float)rdx, (float)rdz,
-                             (float)(rdx * rdx), (float)(rdz * rdz), nx, ny, nz};
+                             (float)(rdx * rdx), (float)(rdz * rdz), (float)(0.25 * rdx), (float)(0.25 * rdz),
+                             nx, ny, nz, pl->s_rows + cf::kRowPad * 8};
     std::vector<double> dyc(std::max(ny - 1, 1), 1.0);
     for (int j = 0; j + 1 < ny; ++j) dyc[j] = pl->dyc[j];
     if ((st = upload(pl, &pl->d_dyc, dyc)) != CF_OK) return bail(st);

@@ -12,30 +12,15 @@
 // plane-below values of the thread's own column from registers, so the input
 // ring keeps two planes (j, j+1).  Stage 2 runs two planes behind stage 1 (the
 // ub ring keeps three planes), so within one barrier interval the two stages
-// are independent and their LDS reads and arithmetic interleave.  The first
-// planes of a chunk get the carries from a short prologue over the two planes
-// below it.
+// are independent and their LDS reads and arithmetic interleave: neither has a
+// branch (the row factors hold the walls, see YRow).  A chunk starts four
+// iterations early with nothing in the carries: each iteration makes the next
+// one's valid, and the first results stored are those of its first plane.
 #pragma once
 
 #include "cf_step_kernels.h"
 
 namespace cf {
-
-// x-y and y-z edge products at the upper face of plane j (face j+1): the
-// expressions momentum_rhs uses for its carried products.  Zero at and above
-// the top wall and below the bottom wall.
-template <typename T, class Acc>
-__device__ __forceinline__ FaceFlux<T> upper_face_flux(const Acc& A, const YTab<T>& Y, int j, int ny) {
-  FaceFlux<T> f{T(0), T(0)};
-  if (j >= 0 && j < ny - 1) {
-    const T h = T(0.5);
-    const T a = Y.wl(j), b = Y.wu(j);
-    const T v0 = A.v(0, 0, 0);
-    f.exy = (A.u(0, 0, 0) * a + A.u(1, 0, 0) * b) * (h * (v0 + A.v(0, 0, 1)));
-    f.eyz = (A.w(0, 0, 0) * a + A.w(1, 0, 0) * b) * (h * (v0 + A.v(0, 1, 0)));
-  }
-  return f;
-}
 
 // Two-plane LDS ring (planes j and j+1, row stride SXX) with the thread's own
 // column at plane j-1 held in registers.  Off-column values of plane j-1 are
@@ -70,28 +55,23 @@ struct ColState {
 template <typename T, int UX>
 __device__ __forceinline__ void rk_stage1_point(const T* su, const T* sv, const T* sw, T* bu, T* bv, T* bw, int s0,
                                                 int sp, int ubase, int boff, ColState<T>& st, const Geo<T>& g,
-                                                const YTab<T>& Y, int j, T dt, T nu, T fx) {
-  const int ny = g.ny;
+                                                const YRow<T>& Y, int j, T dt, T nu, T fx) {
   const Ring2Acc<T, UX> A{su, sv, sw, s0, sp, ubase, st.um, st.vm, st.wm};
   const T uc = A.u(0, 0, 0), vc = A.v(0, 0, 0), wc = A.w(0, 0, 0);
-  T ou = T(0), ov = T(0), ow = T(0);
-  FaceFlux<T> up{T(0), T(0)};
-  if (j >= 0 && j < ny) {
-    const RhsOut<T> r = momentum_rhs<T>(A, g, Y, j, nu, fx, true, st.c, up);
-    ou = uc + dt * r.ru;
-    ov = (j == ny - 1) ? T(0) : vc + dt * r.rv;
-    ow = wc + dt * r.rw;
-  }
+  FaceFlux<T> up;
+  const RhsOut<T> r = momentum_rhs<T>(A, g, Y, nu, fx, st.c, up);
+  const bool in = j >= 0 && j < g.ny;
+  const T ou = uc + dt * r.ru, ov = vc + dt * r.rv, ow = wc + dt * r.rw;
   st.c = up;
   st.um = uc;
   st.vm = vc;
   st.wm = wc;
-  bu[boff] = ou;
-  bv[boff] = ov;
-  bw[boff] = ow;
+  bu[boff] = in ? ou : T(0);
+  bv[boff] = in && j != g.ny - 1 ? ov : T(0);
+  bw[boff] = in ? ow : T(0);
 }
 
-// Most planes of one y-chunk (the metric rows of a chunk are staged in LDS).
+// Most planes of one y-chunk.
 constexpr int kRkfMaxChunk = 128;
 
 template <int TX, int TZ>
@@ -103,8 +83,14 @@ struct RkFusedTile {
   static constexpr int PER = (UPL + TH - 1) / TH;                // input values per thread per plane
 };
 
-// At least four waves per SIMD: the register cap this sets (128 VGPRs, some
-// spilled in FP64) costs less than the latency hiding fewer waves would lose.
+// At least four waves per SIMD in FP64 (128 VGPRs, five spilled) and six in FP32
+// (three blocks per CU).  The row factors in scalar registers, the walls without
+// branches and the folded averages took the FP64 pass from 360 to 281 VALU and 57
+// to 40 LDS instructions per wave and plane and from 2.18 to 1.88 ms on
+// 1024x256x512 (6.44 GB, 3.4 TB/s), and FP32 from 3.78 to 3.07 ms on
+// 1024x384x1024.  VALU issue takes 0.63 of the cycles and LDS 0.45, at a 2.0 GHz
+// clock; the three waves with outer cells finish last.  Outer cells first, or
+// with a raised priority, are 2-4 % slower.
 // The tile index is remapped (xcd_slab_block over the whole grid) so that each
 // XCD walks one contiguous run of tiles and neighbouring tiles share the halo
 // lines in one L2 (runs within each y-chunk instead: within 1.5 %, either way).
@@ -112,7 +98,7 @@ struct RkFusedTile {
 // (the FP64 pass on 1024x256x512: about 2 % faster).
 // cy: planes of a block's chunk, at most kRkfMaxChunk (see chunk_planes).
 template <typename T, int TX, int TZ, bool NT>
-__global__ void __launch_bounds__(TX * TZ, 4)
+__global__ void __launch_bounds__(TX * TZ, sizeof(T) == 8 ? 4 : 6)
 k_rk2_fused(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w, T* uo, T* vo, T* wo,
             Geo<T> g, T dt, T nu, T fx, int cy) {
   using Tl = RkFusedTile<TX, TZ>;
@@ -120,7 +106,6 @@ k_rk2_fused(const T* __restrict__ u, const T* __restrict__ v, const T* __restric
   static_assert(Tl::NRING <= TH, "the grown tile's outer cells must fit one pass of the block");
   __shared__ T su[2 * UPL], sv[2 * UPL], sw[2 * UPL];
   __shared__ T bu[3 * EPL], bv[3 * EPL], bw[3 * EPL];
-  __shared__ T sy[4 * (kRkfMaxChunk + 4)];
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const int ntx = (nx + TX - 1) / TX, ntz = (nz + TZ - 1) / TZ;
   int b = xcd_slab_block(blockIdx.x, gridDim.x);
@@ -183,90 +168,46 @@ k_rk2_fused(const T* __restrict__ u, const T* __restrict__ v, const T* __restric
   }
   const int ubB = (ezB + 1) * UX + exB + 1, eB = ezB * EX + exB;
 #define CF_US(jj) (((jj) & 1) * UPL)
-#define CF_BS(jj) ((((jj) + 3) % 3) * EPL)
+#define CF_BS(jj) ((((jj) + 6) % 3) * EPL)
 
+  ColState<T> sA{}, sB{}, s2{};
   CF_RKF_FETCH(j0 - 2)
   CF_RKF_STORE(j0 - 2)
   CF_RKF_FETCH(j0 - 1)
-  CF_RKF_STORE(j0 - 1)
-  const YTab<T> Y = ytab_fill(sy, kRkfMaxChunk + 4, j0 - 2, g);
-  __syncthreads();
-  // stage-1 carries at face j0-1 and the columns at plane j0-2
-  ColState<T> sA, sB;
-  {
-    const Ring2Acc<T, UX> A{su, sv, sw, CF_US(j0 - 2), CF_US(j0 - 1), ubA, T(0), T(0), T(0)};
-    sA.c = upper_face_flux<T>(A, Y, j0 - 2, ny);
-    sA.um = A.u(0, 0, 0);
-    sA.vm = A.v(0, 0, 0);
-    sA.wm = A.w(0, 0, 0);
-    const Ring2Acc<T, UX> B{su, sv, sw, CF_US(j0 - 2), CF_US(j0 - 1), ubB, T(0), T(0), T(0)};
-    sB.c = upper_face_flux<T>(B, Y, j0 - 2, ny);
-    sB.um = B.u(0, 0, 0);
-    sB.vm = B.v(0, 0, 0);
-    sB.wm = B.w(0, 0, 0);
-  }
-  CF_RKF_FETCH(j0)
-  __syncthreads();
-  CF_RKF_STORE(j0)
-  __syncthreads();
-  CF_RKF_FETCH(j0 + 1)
-  rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(j0 - 1), CF_US(j0), ubA, CF_BS(j0 - 1) + eA, sA, g, Y, j0 - 1,
-                         dt, nu, fx);
-  if (hasB)
-    rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(j0 - 1), CF_US(j0), ubB, CF_BS(j0 - 1) + eB, sB, g, Y,
-                           j0 - 1, dt, nu, fx);
-  __syncthreads();
-  CF_RKF_STORE(j0 + 1)
-  __syncthreads();
-  CF_RKF_FETCH(j0 + 2)
-  rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(j0), CF_US(j0 + 1), ubA, CF_BS(j0) + eA, sA, g, Y, j0, dt, nu,
-                         fx);
-  if (hasB)
-    rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(j0), CF_US(j0 + 1), ubB, CF_BS(j0) + eB, sB, g, Y, j0, dt,
-                           nu, fx);
-  __syncthreads();
-  // stage-2 carries at face j0 and the own column of ub at plane j0-1
-  ColState<T> s2;
-  {
-    const Ring2Acc<T, EX> A{bu, bv, bw, CF_BS(j0 - 1), CF_BS(j0), eA, T(0), T(0), T(0)};
-    s2.c = upper_face_flux<T>(A, Y, j0 - 1, ny);
-    s2.um = A.u(0, 0, 0);
-    s2.vm = A.v(0, 0, 0);
-    s2.wm = A.w(0, 0, 0);
-  }
   const T hh = T(0.5), hd = T(0.5) * dt;
   // iteration s: stage 1 at plane s+1 and stage 2 at plane s-1, independent of
-  // each other within the barrier interval (three ub planes in LDS)
+  // each other within the barrier interval (three ub planes in LDS).  Valid from
+  // s = j0-3 on: the carries of stage 1; from j0-2: ub of plane j0-1; from j0:
+  // the carries of stage 2; from j0+1: the results
   T p0u = T(0), p0v = T(0), p0w = T(0);
-  for (int s = j0; s <= j1; ++s) {
+  for (int s = j0 - 3; s <= j1; ++s) {
     CF_RKF_STORE(s + 2)
     __syncthreads();
     CF_RKF_FETCH(s + 3)
+    const YRow<T> Y1 = load_row(g.rows, s + 1), Y2 = load_row(g.rows, s - 1);
     const T c0u = sA.um, c0v = sA.vm, c0w = sA.wm;  // u, v, w of this cell at plane s
-    if (s + 1 <= j1) {
-      rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(s + 1), CF_US(s + 2), ubA, CF_BS(s + 1) + eA, sA, g, Y,
-                             s + 1, dt, nu, fx);
-      if (hasB)
-        rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(s + 1), CF_US(s + 2), ubB, CF_BS(s + 1) + eB, sB, g,
-                               Y, s + 1, dt, nu, fx);
-    }
-    if (s > j0) {
+    rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(s + 1), CF_US(s + 2), ubA, CF_BS(s + 1) + eA, sA, g, Y1,
+                           s + 1, dt, nu, fx);
+    {
       const int q = s - 1;
       const Ring2Acc<T, EX> B{bu, bv, bw, CF_BS(q), CF_BS(q + 1), eA, s2.um, s2.vm, s2.wm};
       const T uc = B.u(0, 0, 0), vc = B.v(0, 0, 0), wc = B.w(0, 0, 0);
       FaceFlux<T> up;
-      const RhsOut<T> r = momentum_rhs<T>(B, g, Y, q, nu, fx, true, s2.c, up);
+      const RhsOut<T> r = momentum_rhs<T>(B, g, Y2, nu, fx, s2.c, up);
       s2.c = up;
       s2.um = uc;
       s2.vm = vc;
       s2.wm = wc;
-      if (mine) {
+      if (mine && s > j0) {
         const long id = (long)q * plane + (long)k * nx + i;
         st_once<NT>(hh * (p0u + uc) + hd * r.ru, &uo[id]);
         st_once<NT>((q == ny - 1) ? T(0) : hh * (p0v + vc) + hd * r.rv, &vo[id]);
         st_once<NT>(hh * (p0w + wc) + hd * r.rw, &wo[id]);
       }
     }
+    if (hasB && s < j1)
+      rk_stage1_point<T, UX>(su, sv, sw, bu, bv, bw, CF_US(s + 1), CF_US(s + 2), ubB, CF_BS(s + 1) + eB, sB, g, Y1,
+                             s + 1, dt, nu, fx);
     p0u = c0u;
     p0v = c0v;
     p0w = c0w;

@@ -25,39 +25,35 @@ struct Geo {
   const T* wl;    // dy_{j+1}/(dy_j+dy_{j+1}), ny-1: weight of the lower cell
   const T* wu;    // dy_j/(dy_j+dy_{j+1}), ny-1: weight of the upper cell
   T rdx, rdz, rdx2, rdz2;
+  T rdxq, rdzq;   // rdx / 4, rdz / 4
   int nx, ny, nz;
+  const T* rows;  // YRow rows of planes -kRowPad .. ny + kRowPad - 1; points at plane 0
 };
 
-// The wall-normal metric rows a y-chunk touches (jb .. jb + n - 1 of 1/dy,
-// 1/dyc, wl and wu, zero where a table has no entry), staged in LDS once per
-// block, plus 1/dy of the two wall cells held in registers.  The marching
-// stencils read them from here so that no per-plane global load shares the
-// in-order vector-memory counter with the next plane's prefetch: a wait for
-// such a load would also wait for the prefetch and serialise the pipeline.
+// The wall-normal factors of the momentum stencil at plane j (all zero outside
+// [0, ny)): the interpolation weights carry the 1/2 of the velocity averages
+// they multiply and are zero on the walls, and the wall faces hold 2/dy (the
+// no-slip ghost mirrored about the wall, reached as a neighbour value of 0), so
+// the stencil has no case for the walls.
 template <typename T>
-struct YTab {
-  const T* s;  // 4 x n values in LDS
-  int n, jb;
-  T rdy_bot, rdy_top;
-  __device__ __forceinline__ T rdy(int j) const { return s[j - jb]; }
-  __device__ __forceinline__ T rdyc(int j) const { return s[n + j - jb]; }
-  __device__ __forceinline__ T wl(int j) const { return s[2 * n + j - jb]; }
-  __device__ __forceinline__ T wu(int j) const { return s[3 * n + j - jb]; }
+struct YRow {
+  T rdy, rdyp;   // 1/dy_j, 1/dy_{j+1}
+  T wl, wu;      // half the weights of planes j and j+1 at face j+1
+  T fcm, fc;     // 1/dyc at the lower and the upper face
+  T rdycq;       // 1/(4 dyc) at the upper face, 0 on the wall
+  T pad;
 };
+constexpr int kRowPad = 4;
 
-// Block-cooperative fill of a YTab over rows jb .. jb + n - 1; the caller
-// synchronises before the first read.
+// Row j through the constant address space: j is the same for the whole block,
+// so the row comes by one scalar load into scalar registers.  (Read from LDS it
+// cost seven of the 25 LDS reads of a stencil and as many vector registers; a
+// vector load would wait in order behind the next plane's prefetch.)
 template <typename T>
-__device__ __forceinline__ YTab<T> ytab_fill(T* s, int n, int jb, const Geo<T>& g) {
-  for (int t = threadIdx.x; t < n; t += blockDim.x) {
-    const int jj = jb + t;
-    const bool in = jj >= 0 && jj < g.ny - 1;
-    s[t] = (jj >= 0 && jj < g.ny) ? g.rdy[jj] : T(0);
-    s[n + t] = in ? g.rdyc[jj] : T(0);
-    s[2 * n + t] = in ? g.wl[jj] : T(0);
-    s[3 * n + t] = in ? g.wu[jj] : T(0);
-  }
-  return YTab<T>{s, n, jb, g.rdy[0], g.rdy[g.ny - 1]};
+__device__ __forceinline__ YRow<T> load_row(const T* rows, int j) {
+  using CP = const __attribute__((address_space(4))) T*;
+  const CP p = (CP)(uintptr_t)(rows + (long)j * 8);
+  return YRow<T>{p[0], p[1], p[2], p[3], p[4], p[5], p[6], T(0)};
 }
 
 template <typename T>
@@ -65,22 +61,20 @@ struct RhsOut {
   T ru, rv, rw;
 };
 
-// R at point (i, j, k) from an accessor A with A.u(dj, dk, di) etc. returning
-// the neighbour values (dj, dk, di in {-1, 0, 1}); A returns 0 for v on the
-// top wall and for planes outside [0, ny).
 template <typename T>
 struct FaceFlux {
   T exy, eyz;  // x-y and y-z edge products at the upper face of the cell
 };
 
-// `below`: the edge products at the lower face (j) when have_below (they are
-// the upper-face products of plane j-1); `above` receives those of face j+1.
+// R at point (i, j, k) from an accessor A with A.u(dj, dk, di) etc. returning
+// the neighbour values (dj, dk, di in {-1, 0, 1}); A returns 0 for v on the top
+// wall and for planes outside [0, ny).  below: the edge products at the lower
+// face (the upper-face products of plane j-1); above receives those of face
+// j+1.  The averages' factors 1/2 are folded into the difference factors (exact
+// scalings by powers of two).  On the top wall's plane rv is meaningless.
 template <typename T, class Acc>
-__device__ __forceinline__ RhsOut<T> momentum_rhs(const Acc& A, const Geo<T>& g, const YTab<T>& Y, int j, T nu,
-                                                  T fx, bool have_below, FaceFlux<T> below, FaceFlux<T>& above) {
-  const int ny = g.ny;
-  const bool top = (j == ny - 1), bot = (j == 0);
-  const T h = T(0.5);
+__device__ __forceinline__ RhsOut<T> momentum_rhs(const Acc& A, const Geo<T>& g, const YRow<T>& Y, T nu, T fx,
+                                                  FaceFlux<T> below, FaceFlux<T>& above) {
   const T u0 = A.u(0, 0, 0), uip = A.u(0, 0, 1), uim = A.u(0, 0, -1);
   const T ukp = A.u(0, 1, 0), ukm = A.u(0, -1, 0), ukpm = A.u(0, 1, -1);
   const T w0 = A.w(0, 0, 0), wip = A.w(0, 0, 1), wim = A.w(0, 0, -1);
@@ -90,62 +84,39 @@ __device__ __forceinline__ RhsOut<T> momentum_rhs(const Acc& A, const Geo<T>& g,
   const T uj1 = A.u(1, 0, 0), uj1m = A.u(1, 0, -1), wj1 = A.w(1, 0, 0), wj1m = A.w(1, -1, 0);
   const T vj1 = A.v(1, 0, 0);
   const T ujm = A.u(-1, 0, 0), wjm = A.w(-1, 0, 0), vjm = A.v(-1, 0, 0);
-  const T rdy = Y.rdy(j);
   // x-y and y-z edge products at face j+1 (u, w interpolated in y, v in x or z)
-  T exy_i = T(0), exy_im = T(0), eyz_k = T(0), eyz_km = T(0);
-  if (!top) {
-    const T a = Y.wl(j), b = Y.wu(j);
-    exy_i = (u0 * a + uj1 * b) * (h * (v0 + vip));
-    exy_im = (uim * a + uj1m * b) * (h * (vim + v0));
-    eyz_k = (w0 * a + wj1 * b) * (h * (v0 + vkp));
-    eyz_km = (wkm * a + wj1m * b) * (h * (vkm + v0));
-  }
-  T exy_b = T(0), eyz_b = T(0);  // face j (bottom of cell j)
-  if (have_below) {
-    exy_b = below.exy;
-    eyz_b = below.eyz;
-  } else if (!bot) {
-    const T a = Y.wl(j - 1), b = Y.wu(j - 1);
-    exy_b = (ujm * a + u0 * b) * (h * (vjm + A.v(-1, 0, 1)));
-    eyz_b = (wjm * a + w0 * b) * (h * (vjm + A.v(-1, 1, 0)));
-  }
+  const T exy_i = (u0 * Y.wl + uj1 * Y.wu) * (v0 + vip);
+  const T exy_im = (uim * Y.wl + uj1m * Y.wu) * (vim + v0);
+  const T eyz_k = (w0 * Y.wl + wj1 * Y.wu) * (v0 + vkp);
+  const T eyz_km = (wkm * Y.wl + wj1m * Y.wu) * (vkm + v0);
   above.exy = exy_i;
   above.eyz = eyz_k;
-  // x-z edge products at (i+1/2, k+1/2) and the neighbours
-  const T exz = (h * (u0 + ukp)) * (h * (w0 + wip));
-  const T exz_km = (h * (ukm + u0)) * (h * (wkm + wkmp));
-  const T exz_im = (h * (uim + ukpm)) * (h * (wim + w0));
-  // x-momentum
-  const T ucp = h * (uip + u0), ucm = h * (u0 + uim);
-  const T nxu = (ucp * ucp - ucm * ucm) * g.rdx + (exy_i - exy_b) * rdy + (exz - exz_km) * g.rdz;
-  T lu = (uip - T(2) * u0 + uim) * g.rdx2 + (ukp - T(2) * u0 + ukm) * g.rdz2;
-  {
-    const T ft = top ? -T(2) * u0 * Y.rdy_top : (uj1 - u0) * Y.rdyc(j);
-    const T fb = bot ? T(2) * u0 * Y.rdy_bot : (u0 - ujm) * Y.rdyc(j - 1);
-    lu += (ft - fb) * rdy;
-  }
-  // z-momentum
-  const T cwp = h * (wkp + w0), cwm = h * (w0 + wkm);
-  const T nzw = (exz - exz_im) * g.rdx + (eyz_k - eyz_b) * rdy + (cwp * cwp - cwm * cwm) * g.rdz;
-  T lw = (wip - T(2) * w0 + wim) * g.rdx2 + (wkp - T(2) * w0 + wkm) * g.rdz2;
-  {
-    const T ft = top ? -T(2) * w0 * Y.rdy_top : (wj1 - w0) * Y.rdyc(j);
-    const T fb = bot ? T(2) * w0 * Y.rdy_bot : (w0 - wjm) * Y.rdyc(j - 1);
-    lw += (ft - fb) * rdy;
-  }
-  // y-momentum (interior faces only)
-  T rv = T(0);
-  if (!top) {
-    const T ct = h * (vj1 + v0), cb = h * (v0 + vjm);
-    const T nyv = (exy_i - exy_im) * g.rdx + (ct * ct - cb * cb) * Y.rdyc(j) + (eyz_k - eyz_km) * g.rdz;
-    T lv = (vip - T(2) * v0 + vim) * g.rdx2 + (vkp - T(2) * v0 + vkm) * g.rdz2;
-    lv += ((vj1 - v0) * Y.rdy(j + 1) - (v0 - vjm) * rdy) * Y.rdyc(j);
-    rv = -nyv + nu * lv;
-  }
+  // four times the x-z edge products at (i+1/2, k+1/2) and the neighbours
+  const T exz = (u0 + ukp) * (w0 + wip);
+  const T exz_km = (ukm + u0) * (wkm + wkmp);
+  const T exz_im = (uim + ukpm) * (wim + w0);
   RhsOut<T> o;
-  o.ru = -nxu + nu * lu + fx;
-  o.rv = rv;
-  o.rw = -nzw + nu * lw;
+  {
+    const T cp = uip + u0, cm = u0 + uim;
+    const T n = (cp * cp - cm * cm) * g.rdxq + (exz - exz_km) * g.rdzq + (exy_i - below.exy) * Y.rdy;
+    const T l = (uip - T(2) * u0 + uim) * g.rdx2 + (ukp - T(2) * u0 + ukm) * g.rdz2 +
+                ((uj1 - u0) * Y.fc - (u0 - ujm) * Y.fcm) * Y.rdy;
+    o.ru = (nu * l + fx) - n;
+  }
+  {
+    const T cp = wkp + w0, cm = w0 + wkm;
+    const T n = (cp * cp - cm * cm) * g.rdzq + (exz - exz_im) * g.rdxq + (eyz_k - below.eyz) * Y.rdy;
+    const T l = (wip - T(2) * w0 + wim) * g.rdx2 + (wkp - T(2) * w0 + wkm) * g.rdz2 +
+                ((wj1 - w0) * Y.fc - (w0 - wjm) * Y.fcm) * Y.rdy;
+    o.rw = nu * l - n;
+  }
+  {
+    const T cp = vj1 + v0, cm = v0 + vjm;
+    const T n = (cp * cp - cm * cm) * Y.rdycq + (exy_i - exy_im) * g.rdx + (eyz_k - eyz_km) * g.rdz;
+    const T l = (vip - T(2) * v0 + vim) * g.rdx2 + (vkp - T(2) * v0 + vkm) * g.rdz2 +
+                ((vj1 - v0) * Y.rdyp - (v0 - vjm) * Y.rdy) * Y.fc;
+    o.rv = nu * l - n;
+  }
   return o;
 }
 
@@ -200,13 +171,12 @@ struct LdsAcc {
 // NT: outputs, written once, stored non-temporally for large fields (FP64
 // stage 1 on 1024x256x512: 1.37-1.43 -> 1.30 ms).
 template <typename T, int STAGE, int TX, int TZ, bool NT>
-__global__ void __launch_bounds__(TX * TZ)
+__global__ void __launch_bounds__(TX * TZ, sizeof(T) == 8 ? 4 : 6)
 k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
            const T* u0, const T* v0, const T* w0, T* uo, T* vo, T* wo, Geo<T> g, T dt, T nu, T fx, int cy) {
   using Tl = RkTile<TX, TZ>;
   constexpr int PER = (Tl::PLANE + Tl::THREADS - 1) / Tl::THREADS;  // tile values per thread
   __shared__ T su[3 * Tl::PLANE], sv[3 * Tl::PLANE], sw[3 * Tl::PLANE];
-  __shared__ T sy[4 * (kMaxChunk + 2)];
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const int ntx = (nx + TX - 1) / TX, ntz = (nz + TZ - 1) / TZ;
   int b = xcd_slab_block(blockIdx.x, ntx * ntz);
@@ -265,27 +235,31 @@ k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict
     c0 = w0[(long)j0 * plane + pid];
   }
   LdsAcc<T, TX, TZ> A{su, sv, sw, 0, 0, 0, (tz + 1) * Tl::SX + tx + 1};
-  const YTab<T> Y = ytab_fill(sy, kMaxChunk + 2, j0 - 1, g);
   FaceFlux<T> carry{T(0), T(0)};
-  bool have = false;
-  for (int j = j0; j < j1; ++j) {
-    CF_RK_STORE((j + 1) % 3)
+  // plane j0 - 1 only gives the edge products at the chunk's lowest face (its
+  // plane below is not in LDS and what it makes of it is not used)
+  for (int j = j0 - 1; j < j1; ++j) {
+    if (j >= j0) {
+      CF_RK_STORE((j + 1) % 3)
+    }
     __syncthreads();
-    CF_RK_FETCH(j + 2)
+    if (j >= j0) {
+      CF_RK_FETCH(j + 2)
+    }
+    const YRow<T> Y = load_row(g.rows, j);
     T a1 = T(0), b1 = T(0), c1 = T(0);
-    if (STAGE == 2 && mine && j + 1 < j1) {
+    if (STAGE == 2 && mine && j >= j0 && j + 1 < j1) {
       a1 = u0[(long)(j + 1) * plane + pid];
       b1 = (j + 1 < ny - 1) ? v0[(long)(j + 1) * plane + pid] : T(0);
       c1 = w0[(long)(j + 1) * plane + pid];
     }
     A.sm = ((j + 2) % 3) * Tl::PLANE;
-    A.s0 = (j % 3) * Tl::PLANE;
+    A.s0 = ((j + 3) % 3) * Tl::PLANE;
     A.sp = ((j + 1) % 3) * Tl::PLANE;
-    if (mine) {
-      FaceFlux<T> up;
-      const RhsOut<T> r = momentum_rhs<T>(A, g, Y, j, nu, fx, have, carry, up);
-      carry = up;
-      have = true;
+    FaceFlux<T> up;
+    const RhsOut<T> r = momentum_rhs<T>(A, g, Y, nu, fx, carry, up);
+    carry = up;
+    if (mine && j >= j0) {
       const long id = (long)j * plane + pid;
       const bool top = (j == ny - 1);
       const T uc = A.u(0, 0, 0), vc = A.v(0, 0, 0), wc = A.w(0, 0, 0);
@@ -300,9 +274,11 @@ k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict
         st_once<NT>(hh * (c0 + wc) + hd * r.rw, &wo[id]);
       }
     }
-    a0 = a1;
-    b0 = b1;
-    c0 = c1;
+    if (j >= j0) {
+      a0 = a1;
+      b0 = b1;
+      c0 = c1;
+    }
     __syncthreads();
   }
 #undef CF_RK_FETCH

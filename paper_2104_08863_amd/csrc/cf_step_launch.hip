@@ -38,8 +38,8 @@ hipError_t launch_rk_stage(int stage, const T* u, const T* v, const T* w, const 
 // for one more stencil pass).  FP32: 64 x 8 columns, three blocks per CU (half
 // the LDS per value; 6 % faster than 64 x 16 on a 512x384x512 mixed step,
 // 64 x 4 was 15 % slower).  Chunks of at most 128 planes, cut so that the blocks
-// come out in full rounds over the chip: a chunk spends about four plane times
-// before its first plane.  Against chunks of 128, 32 or 8 planes alone: FP64
+// come out in full rounds over the chip: a chunk starts four planes early.
+// Against chunks of 128, 32 or 8 planes alone: FP64
 // 384x97x192 189 -> 137 us, 64^3 40 -> 16 us, FP32 512x192x512 664 -> 513 us.
 template <typename T>
 struct RkfTile {
