@@ -32,188 +32,120 @@ struct AdjGeo {
   const T* dy;    // dy_j
   const T* dyc;   // dyc_{j+1/2}
   const T* rdyc;  // 1/dyc
+  T rdxh, rdzh;   // rdx / 2, rdz / 2
+  const T* rows;  // AdjRow rows of planes -kRowPad .. ny + kRowPad - 1; points at plane 0
 };
 
-// The wall-normal metric rows a y-chunk touches (jb .. jb + n - 1 of 1/dy,
-// 1/dyc, wl and wu, zero where a table has no entry), staged in LDS once per
-// block, plus 1/dy of the two wall cells held in registers.  The marching
-// stencils read them from here so that no per-plane global load shares the
-// in-order vector-memory counter with the next plane's prefetch: a wait for
-// such a load would also wait for the prefetch and serialise the pipeline.
+// The wall-normal factors of the transposed stencil at plane j, zero outside
+// [0, ny) except what plane -1 needs to give the bottom wall's carries (rdyp,
+// fc and rcp).  The weights carry the 1/2 of the velocity averages and are zero
+// on the walls; fc holds 2/dy on the wall faces (see YRow): no case for the
+// walls is left in the stencil.
 template <typename T>
-struct YTab {
-  const T* s;  // 4 x n values in LDS
-  int n, jb;
-  T rdy_bot, rdy_top;
-  __device__ __forceinline__ T rdy(int j) const { return s[j - jb]; }
-  __device__ __forceinline__ T rdyc(int j) const { return s[n + j - jb]; }
-  __device__ __forceinline__ T wl(int j) const { return s[2 * n + j - jb]; }
-  __device__ __forceinline__ T wu(int j) const { return s[3 * n + j - jb]; }
+struct AdjRow {
+  T rdy, rdyp;    // 1/dy_j, 1/dy_{j+1}
+  T wl, wu, wum;  // half the weights at face j+1, and of the upper cell at face j
+  T fc;           // 1/dyc at the upper face, 2/dy on a wall
+  T rc, rcp;      // 1/dyc at faces j+1 and j+2, 0 on the walls
 };
 
-// Block-cooperative fill of a YTab over rows jb .. jb + n - 1; the caller
-// synchronises before the first read.
+// The row by a scalar load (see load_row).
 template <typename T>
-__device__ __forceinline__ YTab<T> ytab_fill(T* s, int n, int jb, const Geo<T>& g) {
-  for (int t = threadIdx.x; t < n; t += blockDim.x) {
-    const int jj = jb + t;
-    const bool in = jj >= 0 && jj < g.ny - 1;
-    s[t] = (jj >= 0 && jj < g.ny) ? g.rdy[jj] : T(0);
-    s[n + t] = in ? g.rdyc[jj] : T(0);
-    s[2 * n + t] = in ? g.wl[jj] : T(0);
-    s[3 * n + t] = in ? g.wu[jj] : T(0);
-  }
-  return YTab<T>{s, n, jb, g.rdy[0], g.rdy[g.ny - 1]};
+__device__ __forceinline__ AdjRow<T> load_adj_row(const T* rows, int j) {
+  using CP = const __attribute__((address_space(4))) T*;
+  const CP p = (CP)(uintptr_t)(rows + (long)j * 8);
+  return AdjRow<T>{p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7]};
 }
 
-// J_R(u)^T lam at point (i, j, k) from an accessor with relative offsets:
-// A.U(dj, dk, di) etc. for the state and A.LU(...) for lam; A returns 0 outside
-// [0, ny) and for v / lam_v on the top wall.
+// J_R(u)^T lam at point (i, j, k) from an accessor with relative offsets in
+// planes j and j+1: A.U(dj, dk, di) etc. for the state and A.LU(...) for lam; A
+// returns 0 outside [0, ny) and for v / lam_v on the top wall.  gv is
+// meaningless on the top wall's plane.
 template <typename T>
 struct AdjOut {
   T gu, gv, gw;
 };
 
-// Lower-face terms of plane j that equal upper-face terms of plane j-1: the
-// x-y and y-z edge factors mu * A(v) at face j (before the wl/wu weight) and
-// the centre term vc * xi_y at centre j.
+// Lower-face terms of plane j that equal upper-face terms of plane j-1: twice
+// the x-y and y-z edge factors mu A(v) at face j, twice the centre term vc xi_y
+// at centre j, and the viscous fluxes of lam_u / W, lam_w / W and lam_v / W
+// through the cell's lower side.
 template <typename T>
 struct AdjCarry {
-  T exy, eyz, cy;
+  T exy, eyz, cy, fu, fw, fv;
 };
 
 template <typename T, class Acc>
-__device__ __forceinline__ AdjOut<T> rhs_adjoint_point(const Acc& A, const AdjGeo<T>& G, const YTab<T>& Y, int j,
-                                                       T nu, bool have, AdjCarry<T> below, AdjCarry<T>& above) {
+__device__ __forceinline__ AdjOut<T> rhs_adjoint_point(const Acc& A, const AdjGeo<T>& G, const AdjRow<T>& Y, T nu,
+                                                       AdjCarry<T>& c) {
   const Geo<T>& g = G.g;
-  const int ny = g.ny;
-  const T h = T(0.5);
   const T rdx = g.rdx, rdz = g.rdz;
-  const bool top = (j == ny - 1), bot = (j == 0);
-  const T ry0 = Y.rdy(j);
-  const T ryp = top ? T(0) : Y.rdy(j + 1);
-  const T rym = bot ? T(0) : Y.rdy(j - 1);
   AdjOut<T> o;
-  // ---------------- u point (i+1/2, j, k)
+  const T U0 = A.U(0, 0, 0), V0 = A.V(0, 0, 0), W0 = A.W(0, 0, 0);
+  const T lu0 = A.LU(0, 0, 0), lv0 = A.LV(0, 0, 0), lw0 = A.LW(0, 0, 0);
+  const T luip = A.LU(0, 0, 1), luim = A.LU(0, 0, -1), lukp = A.LU(0, 1, 0), lukm = A.LU(0, -1, 0);
+  const T lwip = A.LW(0, 0, 1), lwim = A.LW(0, 0, -1), lwkp = A.LW(0, 1, 0), lwkm = A.LW(0, -1, 0);
+  const T lvip = A.LV(0, 0, 1), lvim = A.LV(0, 0, -1), lvkp = A.LV(0, 1, 0), lvkm = A.LV(0, -1, 0);
+  const T lu1 = A.LU(1, 0, 0), lw1 = A.LW(1, 0, 0), lv1 = A.LV(1, 0, 0);
+  const T Uim = A.U(0, 0, -1), Wkm = A.W(0, -1, 0);
+  // the transposed differences mu that consume the edge products, each used by
+  // the two velocities of its product
+  const T qu0 = lu0 * Y.rdy, qu1 = lu1 * Y.rdyp, qw0 = lw0 * Y.rdy, qw1 = lw1 * Y.rdyp;
+  const T muxy = (qu0 - qu1) + (lv0 - lvip) * rdx;
+  const T muyz = (qw0 - qw1) + (lv0 - lvkp) * rdz;
+  const T muxz = (lu0 - lukp) * rdz + (lw0 - lwip) * rdx;
+  const T exy = muxy * (V0 + A.V(0, 0, 1)), eyz = muyz * (V0 + A.V(0, 1, 0));
   {
-    const T uc0 = h * (A.U(0, 0, 0) + A.U(0, 0, -1));
-    const T uc1 = h * (A.U(0, 0, 1) + A.U(0, 0, 0));
-    const T xi0 = (A.LU(0, 0, -1) - A.LU(0, 0, 0)) * rdx;
-    const T xi1 = (A.LU(0, 0, 0) - A.LU(0, 0, 1)) * rdx;
-    T acc = uc0 * xi0 + uc1 * xi1;
-    above.exy = T(0);
-    if (!top) {
-      const T mu = A.LU(0, 0, 0) * ry0 - A.LU(1, 0, 0) * ryp + (A.LV(0, 0, 0) - A.LV(0, 0, 1)) * rdx;
-      above.exy = mu * (h * (A.V(0, 0, 0) + A.V(0, 0, 1)));
-      acc += above.exy * Y.wl(j);
-    }
-    if (!bot) {
-      T e;
-      if (have) {
-        e = below.exy;
-      } else {
-        const T mu = A.LU(-1, 0, 0) * rym - A.LU(0, 0, 0) * ry0 + (A.LV(-1, 0, 0) - A.LV(-1, 0, 1)) * rdx;
-        e = mu * (h * (A.V(-1, 0, 0) + A.V(-1, 0, 1)));
-      }
-      acc += e * Y.wu(j - 1);
-    }
-    {
-      const T mk0 = (A.LU(0, 0, 0) - A.LU(0, 1, 0)) * rdz + (A.LW(0, 0, 0) - A.LW(0, 0, 1)) * rdx;
-      const T mk1 = (A.LU(0, -1, 0) - A.LU(0, 0, 0)) * rdz + (A.LW(0, -1, 0) - A.LW(0, -1, 1)) * rdx;
-      acc += h * (mk0 * (h * (A.W(0, 0, 0) + A.W(0, 0, 1))) + mk1 * (h * (A.W(0, -1, 0) + A.W(0, -1, 1))));
-    }
-    const T l0 = A.LU(0, 0, 0);
-    T lap = (A.LU(0, 0, 1) - T(2) * l0 + A.LU(0, 0, -1)) * g.rdx2 + (A.LU(0, 1, 0) - T(2) * l0 + A.LU(0, -1, 0)) * g.rdz2;
-    const T q0 = l0 * ry0;
-    const T ft = top ? -T(2) * q0 * Y.rdy_top : (A.LU(1, 0, 0) * ryp - q0) * Y.rdyc(j);
-    const T fb = bot ? T(2) * q0 * Y.rdy_bot : (q0 - A.LU(-1, 0, 0) * rym) * Y.rdyc(j - 1);
-    lap += ft - fb;
-    o.gu = -acc + nu * lap;
+    // u point (i+1/2, j, k)
+    const T mk1 = (lukm - lu0) * rdz + (lwkm - A.LW(0, -1, 1)) * rdx;
+    const T s = (U0 + Uim) * (luim - lu0) + (A.U(0, 0, 1) + U0) * (lu0 - luip);
+    const T t = muxz * (W0 + A.W(0, 0, 1)) + mk1 * (Wkm + A.W(0, -1, 1));
+    const T acc = s * G.rdxh + t * T(0.25) + exy * Y.wl + c.exy * Y.wum;
+    const T fu = (qu1 - qu0) * Y.fc;
+    const T lap = (luip - T(2) * lu0 + luim) * g.rdx2 + (lukp - T(2) * lu0 + lukm) * g.rdz2 + (fu - c.fu);
+    o.gu = nu * lap - acc;
+    c.fu = fu;
   }
-  // ---------------- w point (i, j, k+1/2)
   {
-    const T wc0 = h * (A.W(0, 0, 0) + A.W(0, -1, 0));
-    const T wc1 = h * (A.W(0, 1, 0) + A.W(0, 0, 0));
-    const T xi0 = (A.LW(0, -1, 0) - A.LW(0, 0, 0)) * rdz;
-    const T xi1 = (A.LW(0, 0, 0) - A.LW(0, 1, 0)) * rdz;
-    T acc = wc0 * xi0 + wc1 * xi1;
-    {
-      const T m0 = (A.LU(0, 0, 0) - A.LU(0, 1, 0)) * rdz + (A.LW(0, 0, 0) - A.LW(0, 0, 1)) * rdx;
-      const T m1 = (A.LU(0, 0, -1) - A.LU(0, 1, -1)) * rdz + (A.LW(0, 0, -1) - A.LW(0, 0, 0)) * rdx;
-      acc += h * (m0 * (h * (A.U(0, 0, 0) + A.U(0, 1, 0))) + m1 * (h * (A.U(0, 0, -1) + A.U(0, 1, -1))));
-    }
-    above.eyz = T(0);
-    if (!top) {
-      const T mu = (A.LV(0, 0, 0) - A.LV(0, 1, 0)) * rdz + A.LW(0, 0, 0) * ry0 - A.LW(1, 0, 0) * ryp;
-      above.eyz = mu * (h * (A.V(0, 0, 0) + A.V(0, 1, 0)));
-      acc += above.eyz * Y.wl(j);
-    }
-    if (!bot) {
-      T e;
-      if (have) {
-        e = below.eyz;
-      } else {
-        const T mu = (A.LV(-1, 0, 0) - A.LV(-1, 1, 0)) * rdz + A.LW(-1, 0, 0) * rym - A.LW(0, 0, 0) * ry0;
-        e = mu * (h * (A.V(-1, 0, 0) + A.V(-1, 1, 0)));
-      }
-      acc += e * Y.wu(j - 1);
-    }
-    const T l0 = A.LW(0, 0, 0);
-    T lap = (A.LW(0, 0, 1) - T(2) * l0 + A.LW(0, 0, -1)) * g.rdx2 + (A.LW(0, 1, 0) - T(2) * l0 + A.LW(0, -1, 0)) * g.rdz2;
-    const T q0 = l0 * ry0;
-    const T ft = top ? -T(2) * q0 * Y.rdy_top : (A.LW(1, 0, 0) * ryp - q0) * Y.rdyc(j);
-    const T fb = bot ? T(2) * q0 * Y.rdy_bot : (q0 - A.LW(-1, 0, 0) * rym) * Y.rdyc(j - 1);
-    lap += ft - fb;
-    o.gw = -acc + nu * lap;
+    // w point (i, j, k+1/2)
+    const T m1 = (luim - A.LU(0, 1, -1)) * rdz + (lwim - lw0) * rdx;
+    const T s = (W0 + Wkm) * (lwkm - lw0) + (A.W(0, 1, 0) + W0) * (lw0 - lwkp);
+    const T t = muxz * (U0 + A.U(0, 1, 0)) + m1 * (Uim + A.U(0, 1, -1));
+    const T acc = s * G.rdzh + t * T(0.25) + eyz * Y.wl + c.eyz * Y.wum;
+    const T fw = (qw1 - qw0) * Y.fc;
+    const T lap = (lwip - T(2) * lw0 + lwim) * g.rdx2 + (lwkp - T(2) * lw0 + lwkm) * g.rdz2 + (fw - c.fw);
+    o.gw = nu * lap - acc;
+    c.fw = fw;
   }
-  // ---------------- v point (i, face j+1, k), interior faces only
-  o.gv = T(0);
-  above.cy = T(0);
-  if (!top) {
-    const T rc0 = Y.rdyc(j);
-    const T rcm = bot ? T(0) : Y.rdyc(j - 1);
-    const T rcp = (j + 1 < ny - 1) ? Y.rdyc(j + 1) : T(0);
-    T c0;
-    if (have) {
-      c0 = below.cy;
-    } else {
-      const T vc0 = h * (A.V(0, 0, 0) + A.V(-1, 0, 0));
-      c0 = vc0 * (A.LV(-1, 0, 0) * rcm - A.LV(0, 0, 0) * rc0);
-    }
-    const T vc1 = h * (A.V(1, 0, 0) + A.V(0, 0, 0));
-    above.cy = vc1 * (A.LV(0, 0, 0) * rc0 - A.LV(1, 0, 0) * rcp);
-    T acc = c0 + above.cy;
-    const T a = Y.wl(j), b = Y.wu(j);
-    {
-      const T m0 = A.LU(0, 0, 0) * ry0 - A.LU(1, 0, 0) * ryp + (A.LV(0, 0, 0) - A.LV(0, 0, 1)) * rdx;
-      const T m1 = A.LU(0, 0, -1) * ry0 - A.LU(1, 0, -1) * ryp + (A.LV(0, 0, -1) - A.LV(0, 0, 0)) * rdx;
-      acc += h * (m0 * (A.U(0, 0, 0) * a + A.U(1, 0, 0) * b) + m1 * (A.U(0, 0, -1) * a + A.U(1, 0, -1) * b));
-    }
-    {
-      const T m0 = (A.LV(0, 0, 0) - A.LV(0, 1, 0)) * rdz + A.LW(0, 0, 0) * ry0 - A.LW(1, 0, 0) * ryp;
-      const T m1 = (A.LV(0, -1, 0) - A.LV(0, 0, 0)) * rdz + A.LW(0, -1, 0) * ry0 - A.LW(1, -1, 0) * ryp;
-      acc += h * (m0 * (A.W(0, 0, 0) * a + A.W(1, 0, 0) * b) + m1 * (A.W(0, -1, 0) * a + A.W(1, -1, 0) * b));
-    }
-    const T l0 = A.LV(0, 0, 0);
-    T lap = (A.LV(0, 0, 1) - T(2) * l0 + A.LV(0, 0, -1)) * g.rdx2 + (A.LV(0, 1, 0) - T(2) * l0 + A.LV(0, -1, 0)) * g.rdz2;
-    const T q0 = l0 * rc0;
-    const T qp = A.LV(1, 0, 0) * rcp;
-    const T qm = A.LV(-1, 0, 0) * rcm;
-    lap += (qp - q0) * ryp - (q0 - qm) * ry0;
-    o.gv = -acc + nu * lap;
+  {
+    // v point (i, face j+1, k)
+    const T q0 = lv0 * Y.rc, q1 = lv1 * Y.rcp;
+    const T cy = (A.V(1, 0, 0) + V0) * (q0 - q1);
+    const T m1 = luim * Y.rdy - A.LU(1, 0, -1) * Y.rdyp + (lvim - lv0) * rdx;
+    const T m2 = lwkm * Y.rdy - A.LW(1, -1, 0) * Y.rdyp + (lvkm - lv0) * rdz;
+    const T s = muxy * (U0 * Y.wl + A.U(1, 0, 0) * Y.wu) + m1 * (Uim * Y.wl + A.U(1, 0, -1) * Y.wu);
+    const T t = muyz * (W0 * Y.wl + A.W(1, 0, 0) * Y.wu) + m2 * (Wkm * Y.wl + A.W(1, -1, 0) * Y.wu);
+    const T acc = (c.cy + cy) * T(0.5) + s + t;
+    const T fv = (q1 - q0) * Y.rdyp;
+    const T lap = (lvip - T(2) * lv0 + lvim) * g.rdx2 + (lvkp - T(2) * lv0 + lvkm) * g.rdz2 + (fv - c.fv);
+    o.gv = nu * lap - acc;
+    c.cy = cy;
+    c.fv = fv;
   }
+  c.exy = exy;
+  c.eyz = eyz;
   return o;
 }
 
-// LDS accessor: six fields (u, v, w, lam_u, lam_v, lam_w), three plane slots each.
+// LDS accessor: six fields (u, v, w, lam_u, lam_v, lam_w), two plane slots each.
 template <typename T, int TX, int TZ>
 struct AdjLdsAcc {
-  const T* s;      // 6 fields x 3 slots x PLANE
-  int sm, s0, sp;  // slot offsets (in elements) of planes j-1, j, j+1 within a field
+  const T* s;  // 6 fields x 2 slots x PLANE
+  int s0, sp;  // slot offsets (in elements) of planes j and j+1 within a field
   int base;
   static constexpr int SX = TX + 2, PLANE = (TX + 2) * (TZ + 2);
   __device__ __forceinline__ int off(int f, int dj, int dk, int di) const {
-    return f * 3 * PLANE + (dj < 0 ? sm : (dj > 0 ? sp : s0)) + base + dk * SX + di;
+    return f * 2 * PLANE + (dj > 0 ? sp : s0) + base + dk * SX + di;
   }
   __device__ __forceinline__ T U(int dj, int dk, int di) const { return s[off(0, dj, dk, di)]; }
   __device__ __forceinline__ T V(int dj, int dk, int di) const { return s[off(1, dj, dk, di)]; }
@@ -230,8 +162,9 @@ struct AdjPtrs {
 
 // out = s * J_R(state)^T lam (+ A + B when ADD), lam = c1 A (+ c2 B when HASB).
 // 2.5D tiling as in k_rk_stage: a TX x TZ column tile marches over cy planes
-// keeping three planes of the six fields in LDS, the raw values of plane j+2
-// fetched into registers while plane j is computed.  lam is formed only when a
+// keeping planes j and j+1 of the six fields in LDS (what a plane needs of the
+// one below it is carried in registers, see AdjCarry), the raw values of plane
+// j+2 fetched into registers while plane j is computed.  lam is formed only when a
 // plane moves from registers to LDS, and every global load is unconditional
 // (clamped address, masked on the move), so the compiler's waits never cover
 // a load still in flight for a later plane.  Each thread fetches its own cell
@@ -239,20 +172,18 @@ struct AdjPtrs {
 // taken from that fetch (two planes kept in registers) instead of a second
 // load.  Each XCD takes a contiguous run of every y-chunk's tiles
 // (xcd_slab_block; one run over the whole grid is as fast in FP32 and 12 %
-// slower in FP64): the two launches of one adjoint step take 70.8 ms instead
-// of 82.8 on 2048x768x2048 in FP32, 5.7 instead of 6.5 on 1024x256x512 in FP64.
+// slower in FP64).  Bound by its reads: the tiles' halos come to about 1.5 times
+// the fields, mostly from beyond the L2; VALU and LDS are each busy 0.4 of the time.
 // NT: outputs, written once, stored non-temporally for large fields (the
 // two launches of an FP32 adjoint step on 2048x768x2048: 72-74 -> 71.5 ms).
-// FP64: three waves per SIMD (168 VGPRs), the most the LDS of its blocks lets run.
 template <typename T, int TX, int TZ, bool HASB, bool ADD, bool NT>
-__global__ void __launch_bounds__(TX * TZ, sizeof(T) == 8 ? 3 : 1)
+__global__ void __launch_bounds__(TX * TZ)
 k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {
   constexpr int SX = TX + 2, SZ = TZ + 2, PLANE = SX * SZ, TH = TX * TZ;
   constexpr int NHALO = PLANE - TH;                // 2 SX + 2 TZ ring cells
   constexpr int PER = 1 + (NHALO + TH - 1) / TH;  // own cell first, then ring cells
   constexpr int NF = HASB ? 9 : 6;  // raw fields fetched per tile value
-  __shared__ T sm[6 * 3 * PLANE];
-  __shared__ T sy[4 * (kMaxChunk + 2)];
+  __shared__ T sm[6 * 2 * PLANE];
   const T* src[9] = {static_cast<const T*>(P.u),  static_cast<const T*>(P.v),  static_cast<const T*>(P.w),
                      static_cast<const T*>(P.au), static_cast<const T*>(P.av), static_cast<const T*>(P.aw),
                      static_cast<const T*>(P.bu), static_cast<const T*>(P.bv), static_cast<const T*>(P.bw)};
@@ -272,7 +203,8 @@ k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {
   const long plane = (long)nx * nz;
   // tile cells of this thread: q = 0 its own cell (tz+1, tx+1), q >= 1 the
   // ring cells (top row, bottom row, left column, right column)
-  int toff[PER], cidx[PER];
+  unsigned toff[PER];
+  int cidx[PER];
   bool tin[PER];
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
@@ -298,20 +230,21 @@ k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {
     if (gi < 0) gi += nx;
     int gk = (k0 + zz - 1) % nz;
     if (gk < 0) gk += nz;
-    toff[q] = tin[q] ? gk * nx + gi : 0;
+    toff[q] = tin[q] ? unsigned(gk * nx + gi) : 0u;
     cidx[q] = zz * SX + xx;
   }
   T r[NF][PER];
 #define CF_ADJ_FETCH(jj)                                                        \
   {                                                                            \
     const long b_ = (long)min(max((jj), 0), ny - 1) * plane;                   \
-    _Pragma("unroll") for (int q = 0; q < PER; ++q) {                          \
-      _Pragma("unroll") for (int f = 0; f < NF; ++f) r[f][q] = src[f][b_ + toff[q]]; \
+    _Pragma("unroll") for (int f = 0; f < NF; ++f) {                           \
+      const T* p_ = src[f] + b_;                                               \
+      _Pragma("unroll") for (int q = 0; q < PER; ++q) r[f][q] = p_[toff[q]];   \
     }                                                                          \
   }
 #define CF_ADJ_STORE(jj)                                                        \
   {                                                                            \
-    const int sl_ = (((jj) % 3) + 3) % 3;                                      \
+    const int sl_ = (jj) & 1;                                                  \
     const bool pin_ = (jj) >= 0 && (jj) < ny, vin_ = (jj) >= 0 && (jj) < ny - 1; \
     _Pragma("unroll") for (int q = 0; q < PER; ++q) {                          \
       if (tin[q]) {                                                            \
@@ -319,52 +252,46 @@ k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {
         _Pragma("unroll") for (int f = 0; f < 3; ++f) {                        \
           const bool in_ = (f == 1) ? vin_ : pin_;                             \
           const T lam_ = HASB ? c1 * r[3 + f][q] + c2 * r[(6 + f) % NF][q] : c1 * r[3 + f][q]; \
-          sm[f * 3 * PLANE + idx] = in_ ? r[f][q] : T(0);                      \
-          sm[(3 + f) * 3 * PLANE + idx] = in_ ? lam_ : T(0);                   \
+          sm[f * 2 * PLANE + idx] = in_ ? r[f][q] : T(0);                      \
+          sm[(3 + f) * 2 * PLANE + idx] = in_ ? lam_ : T(0);                   \
         }                                                                      \
       }                                                                        \
     }                                                                          \
     if (ADD) {                                                                 \
       _Pragma("unroll") for (int f = 0; f < 3; ++f) {                          \
-        const T ps_ = HASB ? r[3 + f][0] + r[(6 + f) % NF][0] : r[3 + f][0];   \
-        if ((jj) & 1) ps1[f] = ps_; else ps0[f] = ps_;                         \
+        ps0[f] = ps1[f];                                                       \
+        ps1[f] = HASB ? r[3 + f][0] + r[(6 + f) % NF][0] : r[3 + f][0];        \
       }                                                                        \
     }                                                                          \
   }
   const long pid = (long)k * nx + i;
-  // A (+ B) at the own cell of planes with even / odd index, kept from the
-  // move of the plane into LDS for the ADD output
+  // A (+ B) at the own cell of planes j and j+1, kept from the move of the
+  // planes into LDS for the ADD output
   T ps0[3] = {T(0), T(0), T(0)}, ps1[3] = {T(0), T(0), T(0)};
   CF_ADJ_FETCH(j0 - 1)
   CF_ADJ_STORE(j0 - 1)
   CF_ADJ_FETCH(j0)
-  CF_ADJ_STORE(j0)
-  CF_ADJ_FETCH(j0 + 1)
-  AdjLdsAcc<T, TX, TZ> A{sm, 0, 0, 0, (tz + 1) * SX + tx + 1};
+  AdjLdsAcc<T, TX, TZ> A{sm, 0, 0, (tz + 1) * SX + tx + 1};
   T* gu = static_cast<T*>(P.gu);
   T* gv = static_cast<T*>(P.gv);
   T* gw = static_cast<T*>(P.gw);
-  const YTab<T> Y = ytab_fill(sy, kMaxChunk + 2, j0 - 1, g);
-  AdjCarry<T> carry{T(0), T(0), T(0)};
-  bool have = false;
-  for (int j = j0; j < j1; ++j) {
+  AdjCarry<T> carry{};
+  // plane j0 - 1 only gives the carries of the chunk's first plane
+  for (int j = j0 - 1; j < j1; ++j) {
     CF_ADJ_STORE(j + 1)
     __syncthreads();
     CF_ADJ_FETCH(j + 2)
-    A.sm = ((j + 2) % 3) * PLANE;
-    A.s0 = (j % 3) * PLANE;
-    A.sp = ((j + 1) % 3) * PLANE;
-    AdjCarry<T> up;
-    const AdjOut<T> o = rhs_adjoint_point<T>(A, G, Y, j, nu, have, carry, up);
-    carry = up;
-    have = true;
+    const AdjRow<T> Y = load_adj_row(G.rows, j);
+    A.s0 = (j & 1) * PLANE;
+    A.sp = ((j + 1) & 1) * PLANE;
+    const AdjOut<T> o = rhs_adjoint_point<T>(A, G, Y, nu, carry);
     T ou = s * o.gu, ov = s * o.gv, ow = s * o.gw;
     if (ADD) {
-      ou += (j & 1) ? ps1[0] : ps0[0];
-      ov += (j & 1) ? ps1[1] : ps0[1];
-      ow += (j & 1) ? ps1[2] : ps0[2];
+      ou += ps0[0];
+      ov += ps0[1];
+      ow += ps0[2];
     }
-    if (mine) {
+    if (mine && j >= j0) {
       const long id = (long)j * plane + pid;
       st_once<NT>(ou, &gu[id]);
       st_once<NT>((j == ny - 1) ? T(0) : ov, &gv[id]);

@@ -4,19 +4,20 @@
 
 namespace cf {
 
-// Tile of the transposed stencil (six LDS fields x three planes) and chunks of
-// at most 32 planes.  FP64: 32 x 8 columns (51 KB of LDS, three blocks per CU; 64 x 8
-// and 32 x 16 were slower, 32-plane chunks 2 % faster than 64 and 16).  FP32:
-// 64 x 8 columns, 36 % faster than 32 x 8 and ahead of 64 x 16, 128 x 4,
-// 128 x 8 and 32 x 16 on 512x384x512 (half the LDS per value lets the wider
-// tile keep its occupancy while cutting the halo share).
+// Tile of the transposed stencil (six LDS fields x two planes), chunks of at
+// most 32 planes.  Both launches of an adjoint step on 1024x256x512 in FP64: 64 x
+// 4 columns 5.32 ms, 128 x 4 5.52, 32 x 8 5.45 (three planes in LDS and branches
+// for the walls, as before: 5.78), 64 x 8, 32 x 16 and 16 x 16 5.8-6.0; capped at
+// 128 VGPRs for a fourth block per CU they spill and take 6.5-6.8.  FP32 on
+// 1024x384x1024: 128 x 4 columns 8.03 ms, 64 x 8 8.37 (8.99 before), 256 x 4 8.18,
+// 256 x 2 11.7.
 template <typename T>
 struct AdjTile {
-  static constexpr int TX = 32, TZ = 8, BPC = 3;
+  static constexpr int TX = 64, TZ = 4, BPC = 3;
 };
 template <>
 struct AdjTile<float> {
-  static constexpr int TX = 64, TZ = 8, BPC = 3;
+  static constexpr int TX = 128, TZ = 4, BPC = 2;
 };
 
 template <typename T>

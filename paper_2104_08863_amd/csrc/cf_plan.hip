@@ -126,6 +126,8 @@ struct cf_plan {
          *d_kz2 = nullptr, *d_rdyc = nullptr, *d_wl = nullptr, *d_wu = nullptr;
   double* d_rows = nullptr;  // momentum stencil factors by plane (YRow), padded
   float* s_rows = nullptr;
+  double* d_arows = nullptr;  // of the transposed stencil (AdjRow)
+  float* s_arows = nullptr;
   float *s_rdy = nullptr, *s_rdyc = nullptr, *s_wl = nullptr, *s_wu = nullptr;
   float *s_a = nullptr, *s_c = nullptr, *s_kx2 = nullptr, *s_kz2 = nullptr;
   cx<double>*tw_z64 = nullptr, *tw_x64 = nullptr, *twp64 = nullptr;
@@ -1163,6 +1165,22 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
       r[5] = top ? 2.0 * rdy[j] : rdyc[j];
       r[6] = top ? 0.0 : 0.25 * rdyc[j];
     }
+    // the transposed stencil's rows (AdjRow); plane -1 gives the bottom wall's carries
+    std::vector<double> arows(rows.size(), 0.0);
+    for (int j = -1; j < ny; ++j) {
+      double* r = arows.data() + (size_t)(j + cf::kRowPad) * 8;
+      const bool top = j == ny - 1, below = j < 0;
+      r[0] = below ? 0.0 : rdy[j];
+      r[1] = top ? 0.0 : rdy[j + 1];
+      r[2] = top || below ? 0.0 : 0.5 * wl[j];
+      r[3] = top || below ? 0.0 : 0.5 * wu[j];
+      r[4] = j < 1 ? 0.0 : 0.5 * wu[j - 1];
+      r[5] = below ? 2.0 * rdy[0] : top ? 2.0 * rdy[j] : rdyc[j];
+      r[6] = top || below ? 0.0 : rdyc[j];
+      r[7] = j + 1 < ny - 1 ? rdyc[j + 1] : 0.0;
+    }
+    if ((st = upload(pl, &pl->d_arows, arows)) != CF_OK) return bail(st);
+    if ((st = upload(pl, &pl->s_arows, tof(arows))) != CF_OK) return bail(st);
     if ((st = upload(pl, &pl->d_rows, rows)) != CF_OK) return bail(st);
     if ((st = upload(pl, &pl->s_rows, tof(rows))) != CF_OK) return bail(st);
     pl->g64 = cf::Geo<double>{pl->d_rdy, pl->d_rdyc, pl->d_wl, pl->d_wu, rdx, rdz, rdx * rdx, rdz * rdz,
@@ -1175,8 +1193,10 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     if ((st = upload(pl, &pl->d_dyc, dyc)) != CF_OK) return bail(st);
     if ((st = upload(pl, &pl->s_dy, tof(pl->dy))) != CF_OK) return bail(st);
     if ((st = upload(pl, &pl->s_dyc, tof(dyc))) != CF_OK) return bail(st);
-    pl->a64 = cf::AdjGeo<double>{pl->g64, pl->d_dy, pl->d_dyc, pl->d_rdyc};
-    pl->a32 = cf::AdjGeo<float>{pl->g32, pl->s_dy, pl->s_dyc, pl->s_rdyc};
+    pl->a64 = cf::AdjGeo<double>{pl->g64, pl->d_dy, pl->d_dyc, pl->d_rdyc, 0.5 * rdx, 0.5 * rdz,
+                                 pl->d_arows + cf::kRowPad * 8};
+    pl->a32 = cf::AdjGeo<float>{pl->g32, pl->s_dy, pl->s_dyc, pl->s_rdyc, (float)(0.5 * rdx), (float)(0.5 * rdz),
+                                pl->s_arows + cf::kRowPad * 8};
   }
   // Workspace.  Step plans: the stage-1 fields and the two spectral buffers
   // share one block (the stage-1 fields are dead while the pressure is solved);
