@@ -37,9 +37,25 @@ struct FftT {
 CF_HD constexpr int lpad(int e) { return e + (e >> 4); }
 constexpr int lpad_len(int n) { return n + (n >> 4); }
 
+// Orders the LDS accesses of a line's threads (TPL consecutive threads, a power
+// of two).  A line that lies within one wave needs no barrier: a wave's LDS
+// accesses execute in order, and only the compiler has to keep them so.  (Block
+// barriers held all waves of a block to the slowest at every exchange.)
+template <int TPL>
+__device__ __forceinline__ void line_sync() {
+  if constexpr (TPL <= 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
 // Runs passes PASS..np-1 on the registers x (pass PASS input order on entry,
 // last-pass output order on exit).  sl: this line's LDS (N slots).  Every
-// thread of the block must call this (it contains block barriers).
+// thread of the block must call this (it contains block barriers when a line
+// spans waves).
 template <int N, bool INV, typename T, int PASS>
 __device__ __forceinline__ void fft_passes(cx<T>* x, int t, cx<T>* sl, const cx<T>* __restrict__ tw) {
   constexpr RadixPlan P = make_radix_plan(N);
@@ -50,14 +66,14 @@ __device__ __forceinline__ void fft_passes(cx<T>* x, int t, cx<T>* sl, const cx<
   if constexpr (PASS > 0) {
     constexpr int RP = P.r[PASS - 1];
     constexpr int NSP = plan_ns(N, PASS - 1);
-    __syncthreads();
+    line_sync<TPL>();
 #pragma unroll
     for (int q = 0; q < E / RP; ++q) {
       const int b = t + q * TPL;
 #pragma unroll
       for (int r = 0; r < RP; ++r) sl[lpad(st_out(RP, NSP, b, r))] = x[q * RP + r];
     }
-    __syncthreads();
+    line_sync<TPL>();
 #pragma unroll
     for (int q = 0; q < E / R; ++q) {
       const int b = t + q * TPL;
@@ -361,7 +377,7 @@ k_r2c_x(Src src, cx<T>* __restrict__ spec, const cx<T>* tw, const cx<T>* twp, in
   }
   cx<T>* sl = lds + rr * S;
   fft_passes<NH, false, T, 0>(x, tl, sl, tw);
-  __syncthreads();
+  line_sync<F::TPL>();
 #pragma unroll
   for (int q = 0; q < F::E / F::RL; ++q) {
     const int b = tl + q * F::TPL;
