@@ -181,20 +181,48 @@ struct XTw {
 };
 
 // Row sources for the forward real transform: element pair (x_{2m}, x_{2m+1})
-// of row (j, k).
+// of row (j, k), in two steps: load() reads what the pair needs, without a branch
+// (rows next to a wall are clamped, their values replaced in eval()), and eval()
+// computes the pair.  k_r2c_x loads kBatch pairs before it evaluates them: with
+// a branch or a conversion after every pair's loads a wave had one pair's loads
+// in flight at a time.
 // Sources whose kPSum is true also give the FP64 sum over their rows of the
 // pressure they read (psum_pair); k_r2c_x adds it up per block into psum.
 template <typename T, typename Tin>
 struct SrcPlain {
   static constexpr bool kPSum = false;
+  static constexpr int kBatch = 16;
+  using Raw = cx<Tin>;
   const Tin* __restrict__ f;
   int nx, nz;
-  __device__ __forceinline__ cx<T> pair(int j, int k, int m) const {
-    const cx<Tin>* row = reinterpret_cast<const cx<Tin>*>(f + ((long)j * nz + k) * nx);
-    cx<Tin> v = row[m];
-    return mk(T(v.re), T(v.im));
+  __device__ __forceinline__ Raw load(int j, int k, int m) const {
+    return reinterpret_cast<const cx<Tin>*>(f + ((long)j * nz + k) * nx)[m];
   }
+  __device__ __forceinline__ cx<T> eval(const Raw& v, int) const { return mk(T(v.re), T(v.im)); }
 };
+
+// What a divergence needs of a staggered velocity field at a pair.
+template <typename Ts>
+struct DivRaw {
+  cx<Ts> u, v, w, vm, wm;
+  Ts um;
+};
+template <typename Ts>
+__device__ __forceinline__ DivRaw<Ts> div_load(const Ts* u, const Ts* v, const Ts* w, int nx, int nz, int j, int k,
+                                               int m) {
+  const long row = ((long)j * nz + k) * nx;
+  const long rowd = j > 0 ? row - (long)nz * nx : row;
+  const long rowm = ((long)j * nz + (k == 0 ? nz - 1 : k - 1)) * nx;
+  const int im = (m == 0) ? nx - 1 : 2 * m - 1;
+  DivRaw<Ts> d;
+  d.u = reinterpret_cast<const cx<Ts>*>(u + row)[m];
+  d.um = u[row + im];
+  d.w = reinterpret_cast<const cx<Ts>*>(w + row)[m];
+  d.wm = reinterpret_cast<const cx<Ts>*>(w + rowm)[m];
+  d.v = reinterpret_cast<const cx<Ts>*>(v + row)[m];
+  d.vm = reinterpret_cast<const cx<Ts>*>(v + rowd)[m];
+  return d;
+}
 
 // Divergence of a staggered velocity field times `scale` (Eq. (7) right-hand
 // side), produced on the fly: f_i = [(u_i - u_{i-1})/dx + (v_j - v_{j-1})/dy_j
@@ -202,39 +230,24 @@ struct SrcPlain {
 template <typename T, typename Ts>
 struct SrcDiv {
   static constexpr bool kPSum = false;
+  static constexpr int kBatch = 2;
+  using Raw = DivRaw<Ts>;
   const Ts* __restrict__ u;
   const Ts* __restrict__ v;
   const Ts* __restrict__ w;
   const double* __restrict__ rdy;
   double rdx, rdz, scale;
   int nx, ny, nz;
-  __device__ __forceinline__ cx<T> pair(int j, int k, int m) const {
-    const long row = ((long)j * nz + k) * nx;
-    const long plane = (long)nz * nx;
-    const int km = (k == 0) ? nz - 1 : k - 1;
-    const long rowm = ((long)j * nz + km) * nx;
-    const int i0 = 2 * m, i1 = 2 * m + 1, im = (m == 0) ? nx - 1 : 2 * m - 1;
-    const cx<Ts> up = reinterpret_cast<const cx<Ts>*>(u + row)[m];
-    const double uim = double(u[row + im]);
-    const cx<Ts> wp = reinterpret_cast<const cx<Ts>*>(w + row)[m];
-    const cx<Ts> wmp = reinterpret_cast<const cx<Ts>*>(w + rowm)[m];
-    double v0 = 0.0, v1 = 0.0, vm0 = 0.0, vm1 = 0.0;
-    if (j < ny - 1) {
-      const cx<Ts> vp = reinterpret_cast<const cx<Ts>*>(v + row)[m];
-      v0 = double(vp.re);
-      v1 = double(vp.im);
-    }
-    if (j > 0) {
-      const cx<Ts> vmp = reinterpret_cast<const cx<Ts>*>(v + row - plane)[m];
-      vm0 = double(vmp.re);
-      vm1 = double(vmp.im);
-    }
+  __device__ __forceinline__ Raw load(int j, int k, int m) const { return div_load(u, v, w, nx, nz, j, k, m); }
+  __device__ __forceinline__ cx<T> eval(const Raw& d, int j) const {
+    const bool top = j == ny - 1, bot = j == 0;
+    const double v0 = top ? 0.0 : double(d.v.re), v1 = top ? 0.0 : double(d.v.im);
+    const double vm0 = bot ? 0.0 : double(d.vm.re), vm1 = bot ? 0.0 : double(d.vm.im);
     const double r = rdy[j];
-    const double f0 = ((double(up.re) - uim) * rdx + (v0 - vm0) * r + (double(wp.re) - double(wmp.re)) * rdz) * scale;
-    const double f1 = ((double(up.im) - double(up.re)) * rdx + (v1 - vm1) * r +
-                       (double(wp.im) - double(wmp.im)) * rdz) * scale;
-    (void)i0;
-    (void)i1;
+    const double f0 = ((double(d.u.re) - double(d.um)) * rdx + (v0 - vm0) * r +
+                       (double(d.w.re) - double(d.wm.re)) * rdz) * scale;
+    const double f1 = ((double(d.u.im) - double(d.u.re)) * rdx + (v1 - vm1) * r +
+                       (double(d.w.im) - double(d.wm.im)) * rdz) * scale;
     return mk(T(f0), T(f1));
   }
 };
@@ -244,6 +257,8 @@ struct SrcDiv {
 template <typename T, typename Ts>
 struct SrcDivW {
   static constexpr bool kPSum = false;
+  static constexpr int kBatch = 2;
+  using Raw = DivRaw<Ts>;
   const Ts* __restrict__ u;
   const Ts* __restrict__ v;
   const Ts* __restrict__ w;
@@ -251,34 +266,31 @@ struct SrcDivW {
   const double* __restrict__ rdyc;
   double rdx, rdz;
   int nx, ny, nz;
-  __device__ __forceinline__ cx<T> pair(int j, int k, int m) const {
-    const long row = ((long)j * nz + k) * nx;
-    const long plane = (long)nz * nx;
-    const int km = (k == 0) ? nz - 1 : k - 1;
-    const long rowm = ((long)j * nz + km) * nx;
-    const int im = (m == 0) ? nx - 1 : 2 * m - 1;
-    const double ry = rdy[j];
-    const cx<Ts> up = reinterpret_cast<const cx<Ts>*>(u + row)[m];
-    const double uim = double(u[row + im]);
-    const cx<Ts> wp = reinterpret_cast<const cx<Ts>*>(w + row)[m];
-    const cx<Ts> wmp = reinterpret_cast<const cx<Ts>*>(w + rowm)[m];
-    double v0 = 0.0, v1 = 0.0, vm0 = 0.0, vm1 = 0.0;
-    if (j < ny - 1) {
-      const cx<Ts> vp = reinterpret_cast<const cx<Ts>*>(v + row)[m];
-      v0 = double(vp.re) * rdyc[j];
-      v1 = double(vp.im) * rdyc[j];
-    }
-    if (j > 0) {
-      const cx<Ts> vmp = reinterpret_cast<const cx<Ts>*>(v + row - plane)[m];
-      vm0 = double(vmp.re) * rdyc[j - 1];
-      vm1 = double(vmp.im) * rdyc[j - 1];
-    }
-    const double f0 = ((double(up.re) - uim) * ry * rdx + (v0 - vm0) * ry + (double(wp.re) - double(wmp.re)) * ry * rdz);
-    const double f1 = ((double(up.im) - double(up.re)) * ry * rdx + (v1 - vm1) * ry +
-                       (double(wp.im) - double(wmp.im)) * ry * rdz);
+  __device__ __forceinline__ Raw load(int j, int k, int m) const { return div_load(u, v, w, nx, nz, j, k, m); }
+  __device__ __forceinline__ cx<T> eval(const Raw& d, int j) const {
+    const bool top = j == ny - 1, bot = j == 0;
+    const double ry = rdy[j], rc = rdyc[top ? 0 : j], rcm = rdyc[bot ? 0 : j - 1];
+    const double v0 = top ? 0.0 : double(d.v.re) * rc, v1 = top ? 0.0 : double(d.v.im) * rc;
+    const double vm0 = bot ? 0.0 : double(d.vm.re) * rcm, vm1 = bot ? 0.0 : double(d.vm.im) * rcm;
+    const double f0 = ((double(d.u.re) - double(d.um)) * ry * rdx + (v0 - vm0) * ry +
+                       (double(d.w.re) - double(d.wm.re)) * ry * rdz);
+    const double f1 = ((double(d.u.im) - double(d.u.re)) * ry * rdx + (v1 - vm1) * ry +
+                       (double(d.w.im) - double(d.wm.im)) * ry * rdz);
     return mk(T(f0), T(f1));
   }
 };
+
+// Start of the nx FP32 values packed into FP64 row k of a plane: the first half
+// of the row's bytes, or the second half of an odd row of up to 4 KiB.  (With
+// every such row in its first half the accesses fall on part of the memory
+// channels: mixed 512x192x512, residual transform 285 -> 270 us, its two inverse
+// transforms 228 -> 208 us; rows of 8 and 16 KiB gain nothing and lose 0.3 %.)
+CF_HD const float* rows32(const double* row, int k, int nx) {
+  return reinterpret_cast<const float*>(row) + (nx <= 512 ? (k & 1) * nx : 0);
+}
+CF_HD float* rows32(double* row, int k, int nx) {
+  return reinterpret_cast<float*>(row) + (nx <= 512 ? (k & 1) * nx : 0);
+}
 
 // FP64 residual of the Poisson equation, r = f - L_h p (7-point staggered
 // Laplacian, no flux through the walls: a_0 = c_{ny-1} = 0), rounded to T.
@@ -288,11 +300,17 @@ struct SrcDivW {
 // psum: the correction solve uses it to restore the gauge mean_W(p) = 0 that
 // the FP32 transforms of the previous solve leave off by their rounding.
 // Tp = float: every row of the FP64 array p holds that row's nx values as
-// FP32 in its first half (the FP32 solve's output before the first correction
-// is added; see DstRows32), read exactly as FP64.
+// FP32 in one half of its bytes (the FP32 solve's output before the first
+// correction is added; see rows32), read exactly as FP64.
 template <typename T, typename In, typename Tp = double>
 struct SrcResidual {
   static constexpr bool kPSum = true;
+  static constexpr int kBatch = 2;
+  struct Raw {
+    typename In::Raw f;
+    cx<Tp> c, kp, km, jp, jm;
+    Tp im, ip;
+  };
   In in;
   const double* __restrict__ p;
   const double* __restrict__ a;
@@ -300,42 +318,39 @@ struct SrcResidual {
   double rdx2, rdz2;
   int nx, ny, nz;
   double* __restrict__ psum;  // [blocks of k_r2c_x]: the block's sum of p
-  // values 2m, 2m+1 and value i of the row starting at FP64 offset row
-  __device__ __forceinline__ cx<double> pv2(long row, int m) const {
-    const cx<Tp> v = reinterpret_cast<const cx<Tp>*>(reinterpret_cast<const Tp*>(p + row))[m];
-    return mk(double(v.re), double(v.im));
+  // start of row (j, k): of its FP64 values, or of its packed FP32 ones
+  __device__ __forceinline__ const Tp* prow(int j, int k) const {
+    const double* row = p + ((long)j * nz + k) * nx;
+    if constexpr (sizeof(Tp) == 4) return rows32(row, k, nx);
+    else return row;
   }
-  __device__ __forceinline__ double pv1(long row, int i) const {
-    return double(reinterpret_cast<const Tp*>(p + row)[i]);
-  }
-  __device__ __forceinline__ double psum_pair(int j, int k, int m) const {
-    const cx<double> pc = pv2(((long)j * nz + k) * nx, m);
-    return pc.re + pc.im;
-  }
-  __device__ __forceinline__ cx<T> pair(int j, int k, int m) const {
-    const long plane = (long)nz * nx;
-    const long row = ((long)j * nz + k) * nx;
+  __device__ __forceinline__ double psum_pair(const Raw& d) const { return double(d.c.re) + double(d.c.im); }
+  __device__ __forceinline__ Raw load(int j, int k, int m) const {
+    using V = const cx<Tp>*;
     const int kp = (k + 1 == nz) ? 0 : k + 1, km = (k == 0) ? nz - 1 : k - 1;
-    const long rowp = ((long)j * nz + kp) * nx, rowm = ((long)j * nz + km) * nx;
-    const int i0 = 2 * m, i1 = 2 * m + 1;
-    const int im = (m == 0) ? nx - 1 : i0 - 1, ip = (i1 + 1 == nx) ? 0 : i1 + 1;
-    const cx<double> fd = in.pair(j, k, m);
-    const cx<double> pc = pv2(row, m);
-    const double pim = pv1(row, im), pip = pv1(row, ip);
-    const cx<double> pkp = pv2(rowp, m);
-    const cx<double> pkm = pv2(rowm, m);
-    double l0 = (pc.im - 2.0 * pc.re + pim) * rdx2 + (pkp.re - 2.0 * pc.re + pkm.re) * rdz2;
-    double l1 = (pip - 2.0 * pc.im + pc.re) * rdx2 + (pkp.im - 2.0 * pc.im + pkm.im) * rdz2;
-    if (j + 1 < ny) {
-      const cx<double> q = pv2(row + plane, m);
-      l0 += c[j] * (q.re - pc.re);
-      l1 += c[j] * (q.im - pc.im);
-    }
-    if (j > 0) {
-      const cx<double> q = pv2(row - plane, m);
-      l0 += a[j] * (q.re - pc.re);
-      l1 += a[j] * (q.im - pc.im);
-    }
+    const int im = (m == 0) ? nx - 1 : 2 * m - 1, ip = (2 * m + 2 == nx) ? 0 : 2 * m + 2;
+    const Tp* row = prow(j, k);
+    Raw d;
+    d.f = in.load(j, k, m);
+    d.c = reinterpret_cast<V>(row)[m];
+    d.im = row[im];
+    d.ip = row[ip];
+    d.kp = reinterpret_cast<V>(prow(j, kp))[m];
+    d.km = reinterpret_cast<V>(prow(j, km))[m];
+    // at a wall the row itself: its factor there is 0
+    d.jp = reinterpret_cast<V>(prow(j + 1 < ny ? j + 1 : j, k))[m];
+    d.jm = reinterpret_cast<V>(prow(j > 0 ? j - 1 : j, k))[m];
+    return d;
+  }
+  __device__ __forceinline__ cx<T> eval(const Raw& d, int j) const {
+    const cx<double> fd = in.eval(d.f, j);
+    const double c0 = double(d.c.re), c1 = double(d.c.im);
+    double l0 = (c1 - 2.0 * c0 + double(d.im)) * rdx2 + (double(d.kp.re) - 2.0 * c0 + double(d.km.re)) * rdz2;
+    double l1 = (double(d.ip) - 2.0 * c1 + c0) * rdx2 + (double(d.kp.im) - 2.0 * c1 + double(d.km.im)) * rdz2;
+    l0 += c[j] * (double(d.jp.re) - c0);
+    l1 += c[j] * (double(d.jp.im) - c1);
+    l0 += a[j] * (double(d.jm.re) - c0);
+    l1 += a[j] * (double(d.jm.im) - c1);
     return mk(T(fd.re - l0), T(fd.im - l1));
   }
 };
@@ -364,17 +379,23 @@ k_r2c_x(Src src, cx<T>* __restrict__ spec, const cx<T>* tw, const cx<T>* twp, in
   const int rr = threadIdx.x / F::TPL;
   const int k = k0 + rr;
   const bool ok = k < nz;
+  const int kc = ok ? k : nz - 1;  // rows past the last one repeat it and are not written
   cx<T> x[F::E];
   double psum = 0.0;
+  constexpr int NB = F::E < Src::kBatch ? F::E : Src::kBatch;
 #pragma unroll
-  for (int q = 0; q < F::E / F::R0; ++q) {
-    const int b = tl + q * F::TPL;
+  for (int e0 = 0; e0 < F::E; e0 += NB) {
+    typename Src::Raw raw[NB];
 #pragma unroll
-    for (int r = 0; r < F::R0; ++r) {
-      x[q * F::R0 + r] = ok ? src.pair(j, k, st_in(NH, F::R0, b, r)) : mk(T(0), T(0));
-      if constexpr (Src::kPSum) psum += ok ? src.psum_pair(j, k, st_in(NH, F::R0, b, r)) : 0.0;
+    for (int e = e0; e < e0 + NB && e < F::E; ++e)
+      raw[e - e0] = src.load(j, kc, st_in(NH, F::R0, tl + e / F::R0 * F::TPL, e % F::R0));
+#pragma unroll
+    for (int e = e0; e < e0 + NB && e < F::E; ++e) {
+      x[e] = src.eval(raw[e - e0], j);
+      if constexpr (Src::kPSum) psum += src.psum_pair(raw[e - e0]);
     }
   }
+  if (!ok) psum = 0.0;
   cx<T>* sl = lds + rr * S;
   fft_passes<NH, false, T, 0>(x, tl, sl, tw);
   line_sync<F::TPL>();
@@ -429,7 +450,7 @@ struct DstPlain {
 };
 
 // FP32 output packed into FP64 rows: row (j, k) of the FP64 array p receives
-// its nx values as FP32 in the first half of its own bytes.  An FP32 solve
+// its nx values as FP32 in one half of its own bytes (rows32).  An FP32 solve
 // that a refinement will correct stores its result this way: the values are
 // exactly those the FP64 store would hold, at half the bytes written here and
 // read by the residual and the accumulation that follow.
@@ -439,7 +460,7 @@ struct DstRows32 {
   double* __restrict__ p;
   int nx, nz;
   __device__ __forceinline__ void put(int j, int k, int m, cx<T> v) const {
-    float* row = reinterpret_cast<float*>(p + ((long)j * nz + k) * nx);
+    float* row = rows32(p + ((long)j * nz + k) * nx, k, nx);
     reinterpret_cast<cx<float>*>(row)[m] = mk(float(v.re), float(v.im));
   }
 };
@@ -468,7 +489,7 @@ struct DstAccumRows32 {
   double* __restrict__ p;
   int nx, nz;
   __device__ __forceinline__ cx<float> pre(int j, int k, int m) const {
-    const float* row = reinterpret_cast<const float*>(p + ((long)j * nz + k) * nx);
+    const float* row = rows32(static_cast<const double*>(p) + ((long)j * nz + k) * nx, k, nx);
     return reinterpret_cast<const cx<float>*>(row)[m];
   }
   __device__ __forceinline__ void put(int j, int k, int m, cx<float> v, cx<float> old) const {

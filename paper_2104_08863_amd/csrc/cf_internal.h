@@ -75,7 +75,7 @@ template <typename T>
 hipError_t launch_c2r_accum(int nh, const cx<T>* spec, double* p, const cx<T>* tw, const cx<T>* twp, int ny,
                             int nz, T scale, bool p32, hipStream_t s);
 
-// Inverse real transform stored as FP32 into the first half of each FP64 row
+// Inverse real transform stored as FP32 into one half of each FP64 row
 // of p (a solve whose result a refinement pass corrects next).
 template <typename T>
 hipError_t launch_c2r_rows32(int nh, const cx<T>* spec, double* p, const cx<T>* tw, const cx<T>* twp, int ny,

@@ -665,7 +665,7 @@ struct MixedRhs {
 // p += S32(f - L_h p) with the residual formed in FP64.  S32 runs the transforms
 // and the bulk PDD in FP32 and the FP64 line set in FP64.  p0 comes out of an
 // FP32 transform, so when a refinement follows it is stored as FP32, packed
-// into the first half of each FP64 row of p (the same values at half the
+// into one half of each FP64 row of p (the same values at half the
 // bytes); the residual reads it from there and the first correction writes
 // the FP64 sum over it.
 cf_status poisson_mixed(cf_plan* pl, MixedRhs rhs, double* p, hipStream_t s) {
