@@ -50,9 +50,39 @@ constexpr RadixPlan make_radix_plan(int n) {
   return p;
 }
 
+// FP64 radices with fewer elements per thread where that costs no pass: 12 for
+// N = 3 * 2^a up to 768 (4s and a last 6 or 12; 24 elements are 96 registers and
+// leave half-filled waves in the x transforms), 4 and 8 for N = 16, 32 and 64
+// (the chain of one thread is most of a short transform's time).
+constexpr RadixPlan make_radix_plan_fp64(int n) {
+  RadixPlan p{0, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, 1};
+  if (n % 3 == 0 && n >= 24 && n <= 768) {
+    int m = n;
+    while (m > 12) { p.r[p.np++] = 4; m /= 4; }
+    p.r[p.np++] = m;  // 6 or 12
+    p.e = 12;
+    return p;
+  }
+  if (n == 16 || n == 32 || n == 64) {
+    p.np = 2;
+    p.r[0] = n == 16 ? 4 : 8;
+    p.r[1] = n / p.r[0];
+    p.e = p.r[0];
+    return p;
+  }
+  return make_radix_plan(n);
+}
+
+// The plan of a transform in T.
+template <typename T>
+constexpr RadixPlan radix_plan(int n) {
+  return sizeof(T) == 8 ? make_radix_plan_fp64(n) : make_radix_plan(n);
+}
+
 // Sub-transform length before pass `pass`.
+template <typename T>
 constexpr int plan_ns(int n, int pass) {
-  RadixPlan p = make_radix_plan(n);
+  RadixPlan p = radix_plan<T>(n);
   int ns = 1;
   for (int i = 0; i < pass; ++i) ns *= p.r[i];
   return ns;
@@ -120,6 +150,49 @@ template <bool INV, typename T> CF_HD void bfly8(cx<T>* x) {
   }
 }
 
+// 6 = 3 x 2 and 12 = 3 x 4: DFT_3 over x[n2 + R2 n1], twiddles w_{3 R2}^{n2 k1},
+// DFT_R2 over n2 into y[k1 + 3 k2].
+template <bool INV, typename T> CF_HD void bfly6(cx<T>* x) {
+  const T h = T(0.86602540378443864676372317075294);  // sin(pi / 3)
+  const T sg = INV ? T(1) : T(-1);
+  cx<T> a[3] = {x[0], x[2], x[4]}, b[3] = {x[1], x[3], x[5]};
+  bfly3<INV>(a);
+  bfly3<INV>(b);
+  b[1] = cmul(b[1], mk(T(0.5), sg * h));
+  b[2] = cmul(b[2], mk(T(-0.5), sg * h));
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    x[k] = a[k] + b[k];
+    x[k + 3] = a[k] - b[k];
+  }
+}
+
+template <bool INV, typename T> CF_HD void bfly12(cx<T>* x) {
+  const T h = T(0.86602540378443864676372317075294);  // sin(pi / 3)
+  const T sg = INV ? T(1) : T(-1);
+  cx<T> y[4][3];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    y[n][0] = x[n];
+    y[n][1] = x[n + 4];
+    y[n][2] = x[n + 8];
+    bfly3<INV>(y[n]);
+  }
+  y[1][1] = cmul(y[1][1], mk(h, sg * T(0.5)));
+  y[1][2] = cmul(y[1][2], mk(T(0.5), sg * h));
+  y[2][1] = cmul(y[2][1], mk(T(0.5), sg * h));
+  y[2][2] = cmul(y[2][2], mk(T(-0.5), sg * h));
+  y[3][1] = mul_mi<INV>(y[3][1]);
+  y[3][2] = y[3][2] * T(-1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    cx<T> z[4] = {y[0][k], y[1][k], y[2][k], y[3][k]};
+    bfly4<INV>(z);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[k + 3 * q] = z[q];
+  }
+}
+
 template <bool INV, typename T> CF_HD void bfly16(cx<T>* x) {
   cx<T> e[8], o[8];
 #pragma unroll
@@ -150,7 +223,9 @@ template <int R, bool INV, typename T> CF_HD void bfly(cx<T>* x) {
   if constexpr (R == 2) bfly2<INV>(x);
   else if constexpr (R == 3) bfly3<INV>(x);
   else if constexpr (R == 4) bfly4<INV>(x);
+  else if constexpr (R == 6) bfly6<INV>(x);
   else if constexpr (R == 8) bfly8<INV>(x);
+  else if constexpr (R == 12) bfly12<INV>(x);
   else if constexpr (R == 16) bfly16<INV>(x);
 }
 

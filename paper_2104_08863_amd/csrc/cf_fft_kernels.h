@@ -21,9 +21,9 @@
 
 namespace cf {
 
-template <int N>
+template <typename T, int N>
 struct FftT {
-  static constexpr RadixPlan P = make_radix_plan(N);
+  static constexpr RadixPlan P = radix_plan<T>(N);
   static constexpr int E = P.e;
   static constexpr int TPL = N / E;
   static constexpr int R0 = P.r[0];
@@ -58,14 +58,14 @@ __device__ __forceinline__ void line_sync() {
 // spans waves).
 template <int N, bool INV, typename T, int PASS>
 __device__ __forceinline__ void fft_passes(cx<T>* x, int t, cx<T>* sl, const cx<T>* __restrict__ tw) {
-  constexpr RadixPlan P = make_radix_plan(N);
+  constexpr RadixPlan P = radix_plan<T>(N);
   constexpr int E = P.e;
   constexpr int TPL = N / E;
   constexpr int R = P.r[PASS];
-  constexpr int NS = plan_ns(N, PASS);
+  constexpr int NS = plan_ns<T>(N, PASS);
   if constexpr (PASS > 0) {
     constexpr int RP = P.r[PASS - 1];
-    constexpr int NSP = plan_ns(N, PASS - 1);
+    constexpr int NSP = plan_ns<T>(N, PASS - 1);
     line_sync<TPL>();
 #pragma unroll
     for (int q = 0; q < E / RP; ++q) {
@@ -92,30 +92,33 @@ constexpr int pow2_floor(int n) {
   return p;
 }
 
-constexpr int lds_lines(int n, int tpl, int esize, int budget) {
-  int l = 256 / tpl;
+constexpr int lds_lines(int n, int tpl, int esize, int budget, int threads) {
+  int l = threads / tpl;
   if (l < 1) l = 1;
   while (l > 1 && l * n * esize > budget) l /= 2;
   return l;
 }
 
 // ---------------------------------------------------------------- z (contiguous lines)
-// Lines per block: about 256 threads, within 64 KB of LDS (against 32 KB: the
-// FP32 2048- and 1536-point and FP64 512-point transforms 2-8 % faster).
-template <typename T, int N>
+// Lines per block for large spectra (BIG): about 256 threads, within 64 KB of LDS
+// (against 32 KB: the FP32 2048- and 1536-point and FP64 512-point transforms 2-8 %
+// faster).  Below the size that is streamed one wave of threads: larger blocks
+// would leave CUs idle on small grids (64^3: 66 blocks of 32 lines) and are no
+// faster up to there.
+template <typename T, int N, bool BIG>
 struct ZCfg {
-  static constexpr int LPB = lds_lines(lpad_len(N), FftT<N>::TPL, int(sizeof(cx<T>)), 65536);
-  static constexpr int THREADS = LPB * FftT<N>::TPL;
+  static constexpr int LPB = lds_lines(lpad_len(N), FftT<T, N>::TPL, int(sizeof(cx<T>)), 65536, BIG ? 256 : 64);
+  static constexpr int THREADS = LPB * FftT<T, N>::TPL;
 };
 
 // NT: lines read and written once, streamed (non-temporal) for large spectra:
 // the FP64 512-point transforms on 1024x256x512 take 380 instead of 411-434 us.
 template <typename T, int N, bool INV, bool NT>
-__global__ void __launch_bounds__((ZCfg<T, N>::THREADS))
+__global__ void __launch_bounds__((ZCfg<T, N, NT>::THREADS))
 k_fft_z(const cx<T>* __restrict__ src, cx<T>* __restrict__ dst, const cx<T>* __restrict__ tw, int no,
         int ni) {
-  using F = FftT<N>;
-  constexpr int LPB = ZCfg<T, N>::LPB;
+  using F = FftT<T, N>;
+  constexpr int LPB = ZCfg<T, N, NT>::LPB;
   __shared__ cx<T> lds[LPB * lpad_len(N)];
   const int tl = threadIdx.x % F::TPL;
   const int lb = threadIdx.x / F::TPL;
@@ -152,16 +155,18 @@ struct XCfg {
   // leaves room for them; in FP64 they would halve the blocks per CU).
   static constexpr bool kLdsTw = sizeof(T) == 4;
   static constexpr int TWB = kLdsTw ? (2 * NH + 1) * int(sizeof(cx<T>)) : 0;
-  // rows per block: aim for 128-byte runs of kz in the transposed spectrum
-  static constexpr int KWANT = int(128 / sizeof(cx<T>));
+  // rows per block: aim for 128-byte runs of kz in the transposed spectrum, two
+  // of them where that many short rows do not fill a wave
+  static constexpr int KRUN = int(128 / sizeof(cx<T>));
+  static constexpr int KWANT = KRUN * FftT<T, NH>::TPL < 64 ? 2 * KRUN : KRUN;
   static constexpr int S = lpad(NH) + 1;  // LDS row stride (holds kx = 0..NH at lpad(kx))
   static constexpr int kfit(int k) {
-    return (k > 1 && (k * S * int(sizeof(cx<T>)) > (kLdsTw ? 159744 - TWB : 147456) || k * FftT<NH>::TPL > 1024))
+    return (k > 1 && (k * S * int(sizeof(cx<T>)) > (kLdsTw ? 159744 - TWB : 147456) || k * FftT<T, NH>::TPL > 1024))
                ? kfit(k / 2)
                : k;
   }
   static constexpr int K = kfit(KWANT);
-  static constexpr int THREADS = K * FftT<NH>::TPL;
+  static constexpr int THREADS = K * FftT<T, NH>::TPL;
 };
 
 // The twiddle tables of an x-transform block: copied to LDS when XCfg says so
@@ -358,7 +363,7 @@ struct SrcResidual {
 template <typename T, int NH, typename Src>
 __global__ void __launch_bounds__((XCfg<T, NH>::THREADS))
 k_r2c_x(Src src, cx<T>* __restrict__ spec, const cx<T>* tw, const cx<T>* twp, int ny, int nz) {
-  using F = FftT<NH>;
+  using F = FftT<T, NH>;
   constexpr int K = XCfg<T, NH>::K;
   constexpr int S = XCfg<T, NH>::S;
   constexpr int NKX = NH + 1;
@@ -501,7 +506,7 @@ struct DstAccumRows32 {
 template <typename T, int NH, typename Dst>
 __global__ void __launch_bounds__((XCfg<T, NH>::THREADS))
 k_c2r_x(const cx<T>* __restrict__ spec, Dst dst, const cx<T>* tw, const cx<T>* twp, int ny, int nz, T scale) {
-  using F = FftT<NH>;
+  using F = FftT<T, NH>;
   constexpr int K = XCfg<T, NH>::K;
   constexpr int S = XCfg<T, NH>::S;
   constexpr int NKX = NH + 1;

@@ -22,18 +22,19 @@ bool fft_len_compiled(int n) {
 template <typename T, int N>
 static hipError_t fft_z_n(bool inv, const cx<T>* src, cx<T>* dst, const cx<T>* tw, int no, int ni,
                           hipStream_t s) {
-  using C = ZCfg<T, N>;
-  const long blocks = ((long)no * ni + C::LPB - 1) / C::LPB;
-  if (blocks <= 0) return hipSuccess;
   const bool nt = (long)no * ni * N * (long)sizeof(cx<T>) >= kStreamBytes;
+  const int lpb = nt ? ZCfg<T, N, true>::LPB : ZCfg<T, N, false>::LPB;
+  const int threads = nt ? ZCfg<T, N, true>::THREADS : ZCfg<T, N, false>::THREADS;
+  const long blocks = ((long)no * ni + lpb - 1) / lpb;
+  if (blocks <= 0) return hipSuccess;
   if (inv && nt)
-    hipLaunchKernelGGL((k_fft_z<T, N, true, true>), dim3(blocks), dim3(C::THREADS), 0, s, src, dst, tw, no, ni);
+    hipLaunchKernelGGL((k_fft_z<T, N, true, true>), dim3(blocks), dim3(threads), 0, s, src, dst, tw, no, ni);
   else if (inv)
-    hipLaunchKernelGGL((k_fft_z<T, N, true, false>), dim3(blocks), dim3(C::THREADS), 0, s, src, dst, tw, no, ni);
+    hipLaunchKernelGGL((k_fft_z<T, N, true, false>), dim3(blocks), dim3(threads), 0, s, src, dst, tw, no, ni);
   else if (nt)
-    hipLaunchKernelGGL((k_fft_z<T, N, false, true>), dim3(blocks), dim3(C::THREADS), 0, s, src, dst, tw, no, ni);
+    hipLaunchKernelGGL((k_fft_z<T, N, false, true>), dim3(blocks), dim3(threads), 0, s, src, dst, tw, no, ni);
   else
-    hipLaunchKernelGGL((k_fft_z<T, N, false, false>), dim3(blocks), dim3(C::THREADS), 0, s, src, dst, tw, no, ni);
+    hipLaunchKernelGGL((k_fft_z<T, N, false, false>), dim3(blocks), dim3(threads), 0, s, src, dst, tw, no, ni);
   return hipGetLastError();
 }
 

@@ -28,11 +28,11 @@ std::vector<cx<T>> roots(int n) {
 
 template <int N, bool INV, typename T, int PASS>
 void emul_passes(std::vector<cx<T>>& buf, const cx<T>* tw) {
-  constexpr cf::RadixPlan P = cf::make_radix_plan(N);
+  constexpr cf::RadixPlan P = cf::radix_plan<T>(N);
   constexpr int E = P.e;
   constexpr int TPL = N / E;
   constexpr int R = P.r[PASS];
-  constexpr int NS = cf::plan_ns(N, PASS);
+  constexpr int NS = cf::plan_ns<T>(N, PASS);
   std::vector<cx<T>> nxt(N);
   for (int t = 0; t < TPL; ++t)
     for (int q = 0; q < E / R; ++q) {

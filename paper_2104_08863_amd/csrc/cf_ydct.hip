@@ -28,11 +28,11 @@ struct YdctCfg {
   // fastest of 4, 8, 16 for N = 128, 256 in FP64: more blocks per CU), fewer
   // where LDS would exceed 72 KB
   static constexpr int pick(int l) {
-    return (l > 1 && (l * lpad_len(N) * int(sizeof(cx<T>)) > 73728 || l * FftT<N>::TPL > 1024)) ? pick(l / 2) : l;
+    return (l > 1 && (l * lpad_len(N) * int(sizeof(cx<T>)) > 73728 || l * FftT<T, N>::TPL > 1024)) ? pick(l / 2) : l;
   }
-  static constexpr int want = (64 / FftT<N>::TPL < 8) ? 8 : (64 / FftT<N>::TPL > 64 ? 64 : 64 / FftT<N>::TPL);
+  static constexpr int want = (64 / FftT<T, N>::TPL < 8) ? 8 : (64 / FftT<T, N>::TPL > 64 ? 64 : 64 / FftT<T, N>::TPL);
   static constexpr int LB = pick(want);
-  static constexpr int THREADS = LB * FftT<N>::TPL;
+  static constexpr int THREADS = LB * FftT<T, N>::TPL;
 };
 
 // LDS slot of row j of a line in the reordered sequence v.
@@ -43,11 +43,14 @@ __device__ __forceinline__ int mk_pos(int j) {
 
 // Lines (kx, kz0 .. kz0+LB-1) of layout B (nkx, ny, nz) per block; in place
 // allowed (a block reads its lines completely before writing them).
-template <typename T, int N>
+// Only the moves of the block's rows into and out of LDS cross lines; between
+// them a line's threads order their own accesses (line_sync).  NT: rows read and
+// written once, streamed for large spectra.
+template <typename T, int N, bool NT>
 __global__ void __launch_bounds__((YdctCfg<T, N>::THREADS))
 k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>* __restrict__ wq,
        const T* __restrict__ lam, const T* __restrict__ kx2, const T* __restrict__ kz2, int nz) {
-  using F = FftT<N>;
+  using F = FftT<T, N>;
   constexpr int LB = YdctCfg<T, N>::LB;
   constexpr int TH = YdctCfg<T, N>::THREADS;
   constexpr int S = lpad_len(N);
@@ -64,7 +67,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
 #pragma unroll
     for (int r = 0; r < PT; ++r) {
       const int idx = threadIdx.x + r * TH, q = idx % LB, j = idx / LB;
-      ld[r] = (kz0 + q < nz) ? fin[base + (long)j * nz + q] : mk(T(0), T(0));
+      ld[r] = (kz0 + q < nz) ? ld_once<NT>(&fin[base + (long)j * nz + q]) : mk(T(0), T(0));
     }
 #pragma unroll
     for (int r = 0; r < PT; ++r) {
@@ -83,14 +86,14 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
     for (int r = 0; r < F::R0; ++r) x[q * F::R0 + r] = sl[lpad(st_in(N, F::R0, b, r))];
   }
   fft_passes<N, false, T, 0>(x, tl, sl, tw);
-  __syncthreads();
+  line_sync<F::TPL>();
 #pragma unroll
   for (int q = 0; q < F::E / F::RL; ++q) {
     const int b = tl + q * F::TPL;
 #pragma unroll
     for (int r = 0; r < F::RL; ++r) sl[lpad(b + r * (N / F::RL))] = x[q * F::RL + r];
   }
-  __syncthreads();
+  line_sync<F::TPL>();
   // pairs (m, N-m): DCT-II coefficients, division, DCT-III input
   const int kz = kz0 + qq;
   const T k2 = (kz < nz) ? kx2[kx] + kz2[kz] : T(1);
@@ -114,7 +117,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
       qb[c] = cmul(conj(wb), mk(pb.re + pa.im, pb.im - pa.re));
     }
   }
-  __syncthreads();
+  line_sync<F::TPL>();
 #pragma unroll
   for (int c = 0; c < (NPAIR + F::TPL - 1) / F::TPL; ++c) {
     const int m = tl + c * F::TPL;
@@ -123,7 +126,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
       if (m != 0 && m != N / 2) sl[lpad(N - m)] = qb[c];
     }
   }
-  __syncthreads();
+  line_sync<F::TPL>();
 #pragma unroll
   for (int q = 0; q < F::E / F::R0; ++q) {
     const int b = tl + q * F::TPL;
@@ -131,7 +134,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
     for (int r = 0; r < F::R0; ++r) x[q * F::R0 + r] = sl[lpad(st_in(N, F::R0, b, r))];
   }
   fft_passes<N, true, T, 0>(x, tl, sl, tw);
-  __syncthreads();
+  line_sync<F::TPL>();
   // q_n -> rows: p_2n = q_n, p_(2n+1) = q_(N-1-n), i.e. q_m lands on row
   // 2m (m < N/2) or 2(N-1-m)+1
 #pragma unroll
@@ -148,7 +151,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
 #pragma unroll 4
   for (int idx = threadIdx.x; idx < N * LB; idx += TH) {
     const int q = idx % LB, j = idx / LB;
-    if (kz0 + q < nz) pout[base + (long)j * nz + q] = lds[q * S + lpad(j)];
+    if (kz0 + q < nz) st_once<NT>(lds[q * S + lpad(j)], &pout[base + (long)j * nz + q]);
   }
 }
 
@@ -158,7 +161,10 @@ static hipError_t ydct_n(const cx<T>* fin, cx<T>* pout, const cx<T>* tw, const c
   using C = YdctCfg<T, N>;
   const long blocks = (long)nkx * ((nz + C::LB - 1) / C::LB);
   if (blocks <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_ydct<T, N>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
+  if ((long)nkx * nz * N * (long)sizeof(cx<T>) >= kStreamBytes)
+    hipLaunchKernelGGL((k_ydct<T, N, true>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
+  else
+    hipLaunchKernelGGL((k_ydct<T, N, false>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
   return hipGetLastError();
 }
 
