@@ -99,12 +99,20 @@ __device__ __forceinline__ void st_once(cx<T> v, cx<T>* a) {
   }
 }
 #endif
-// Data size from which the kernels that touch their arrays once (the
-// corrections, the z transforms, the wall-normal solve, the fused RK2 pass's
-// output) take non-temporal loads and stores: the 8 XCDs' L2s together
-// (32 MiB).  Smaller arrays stay cached for the next kernel (streamed, the
-// 64^3 time loop was 2-4 % slower).
+// Data size from which the stencils and corrections take non-temporal loads and
+// stores for the arrays they touch once: the 8 XCDs' L2s together (32 MiB).
+// Smaller arrays stay cached for the next kernel (streamed, the 64^3 time loop
+// was 2-4 % slower).
 constexpr long kStreamBytes = 32L << 20;
+// The spectrum sizes from which the z transforms and the wall-normal solve
+// stream.  What they store without it is partly still in the 256 MB cache behind
+// the L2s when the next kernel of the solve reads it: FP64 Poisson solve, both
+// cached against both streamed, 64 MiB 148 -> 131 us, 109 MiB 232 -> 212, 128 MiB
+// 263 -> 246.  Beyond that two cached neighbours push each other out (193 MiB, the
+// solve cached and the z transforms streamed 949 us, both cached 1031, both
+// streamed 998), and at 1.5 GiB the solve gains by streaming too (1 %).
+constexpr long kStreamZ = 160L << 20;
+constexpr long kStreamSolve = 1280L << 20;
 
 // Compute units of the chip (8 XCDs of 32).
 constexpr int kCus = 256;

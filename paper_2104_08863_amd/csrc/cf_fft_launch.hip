@@ -22,7 +22,7 @@ bool fft_len_compiled(int n) {
 template <typename T, int N>
 static hipError_t fft_z_n(bool inv, const cx<T>* src, cx<T>* dst, const cx<T>* tw, int no, int ni,
                           hipStream_t s) {
-  const bool nt = (long)no * ni * N * (long)sizeof(cx<T>) >= kStreamBytes;
+  const bool nt = (long)no * ni * N * (long)sizeof(cx<T>) >= kStreamZ;
   const int lpb = nt ? ZCfg<T, N, true>::LPB : ZCfg<T, N, false>::LPB;
   const int threads = nt ? ZCfg<T, N, true>::THREADS : ZCfg<T, N, false>::THREADS;
   const long blocks = ((long)no * ni + lpb - 1) / lpb;

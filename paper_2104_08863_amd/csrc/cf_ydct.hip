@@ -161,7 +161,7 @@ static hipError_t ydct_n(const cx<T>* fin, cx<T>* pout, const cx<T>* tw, const c
   using C = YdctCfg<T, N>;
   const long blocks = (long)nkx * ((nz + C::LB - 1) / C::LB);
   if (blocks <= 0) return hipSuccess;
-  if ((long)nkx * nz * N * (long)sizeof(cx<T>) >= kStreamBytes)
+  if ((long)nkx * nz * N * (long)sizeof(cx<T>) >= kStreamSolve)
     hipLaunchKernelGGL((k_ydct<T, N, true>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
   else
     hipLaunchKernelGGL((k_ydct<T, N, false>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
