@@ -30,8 +30,6 @@ template <typename T>
 struct AdjGeo {
   Geo<T> g;
   const T* dy;    // dy_j
-  const T* dyc;   // dyc_{j+1/2}
-  const T* rdyc;  // 1/dyc
   T rdxh, rdzh;   // rdx / 2, rdz / 2
   const T* rows;  // AdjRow rows of planes -kRowPad .. ny + kRowPad - 1; points at plane 0
 };

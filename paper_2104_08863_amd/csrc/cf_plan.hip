@@ -123,12 +123,12 @@ struct cf_plan {
   size_t bytes = 0;
   // device tables (FP64 and FP32 copies)
   double *d_a = nullptr, *d_c = nullptr, *d_dy = nullptr, *d_rdy = nullptr, *d_kx2 = nullptr,
-         *d_kz2 = nullptr, *d_rdyc = nullptr, *d_wl = nullptr, *d_wu = nullptr;
+         *d_kz2 = nullptr, *d_rdyc = nullptr;
   double* d_rows = nullptr;  // momentum stencil factors by plane (YRow), padded
   float* s_rows = nullptr;
   double* d_arows = nullptr;  // of the transposed stencil (AdjRow)
   float* s_arows = nullptr;
-  float *s_rdy = nullptr, *s_rdyc = nullptr, *s_wl = nullptr, *s_wu = nullptr;
+  float* s_rdyc = nullptr;
   float *s_a = nullptr, *s_c = nullptr, *s_kx2 = nullptr, *s_kz2 = nullptr;
   cx<double>*tw_z64 = nullptr, *tw_x64 = nullptr, *twp64 = nullptr;
   // uniform-y transform solve (CF_PLAN_Y_DCT): FFT twiddles of length ny, the
@@ -161,8 +161,7 @@ struct cf_plan {
   int* d_numflag = nullptr;
   // adjoint workspace: projected gradient g* and gb (state precision)
   void *gsu = nullptr, *gsv = nullptr, *gsw = nullptr, *gbu = nullptr, *gbv = nullptr, *gbw = nullptr;
-  double *d_dyc = nullptr;
-  float *s_dy = nullptr, *s_dyc = nullptr;
+  float* s_dy = nullptr;
   cf::AdjGeo<double> a64{};
   cf::AdjGeo<float> a32{};
   cf::Geo<double> g64{};
@@ -226,6 +225,28 @@ cf_status upload(cf_plan* pl, T** out, const std::vector<T>& h) {
   if (e != hipSuccess) return dev_fail(e, "hipMemcpy (plan tables)");
   return CF_OK;
 }
+
+// Device tables collected during plan creation and placed by one allocation and
+// one copy (each of its own cost 20-30 us of a plan's creation, 40 tables 1 ms).
+struct Tables {
+  std::vector<unsigned char> bytes;
+  std::vector<std::pair<void**, size_t>> slots;
+  template <typename T>
+  void add(T** out, const std::vector<T>& h) {
+    bytes.resize((bytes.size() + 255) / 256 * 256);
+    slots.emplace_back(reinterpret_cast<void**>(out), bytes.size());
+    const unsigned char* p = reinterpret_cast<const unsigned char*>(h.data());
+    bytes.insert(bytes.end(), p, p + h.size() * sizeof(T));
+  }
+  // Allocates and fills the device copy; the added pointers are valid after it.
+  cf_status commit(cf_plan* pl) {
+    unsigned char* base = nullptr;
+    cf_status s = upload(pl, &base, bytes);
+    if (s != CF_OK) return s;
+    for (auto& q : slots) *q.first = base + q.second;
+    return CF_OK;
+  }
+};
 
 void free_all(cf_plan* pl) {
   if (!pl->allocs.empty() || !pl->events.empty()) (void)hipDeviceSynchronize();
@@ -591,7 +612,7 @@ hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStrea
   y.iface = iface;
   y.G = pl->G;
   y.special = special;
-  if (pl->d_blocks && !pl->exact_all) {
+  if (pl->d_blocks) {
     y.blocks_exact = pl->d_blocks;
     y.n_exact = (long)pl->blocks_exact.size();
     y.blocks_drop = pl->blocks_drop.empty() ? nullptr : pl->d_blocks + pl->blocks_exact.size();
@@ -1097,17 +1118,22 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
   if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->ev_gin, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->ev_gout, hipEventDisableTiming);
   if (e != hipSuccess) return bail(dev_fail(e, "stream/event creation"));
-  if ((st = upload(pl, &pl->d_a, pl->a)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->d_c, pl->c)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->d_dy, pl->dy)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->d_rdy, rdy)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->d_kx2, pl->kx2)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->d_kz2, pl->kz2)) != CF_OK) return bail(st);
+  Tables tabs;
+  tabs.add(&pl->d_a, pl->a);
+  tabs.add(&pl->d_c, pl->c);
+  tabs.add(&pl->d_dy, pl->dy);
+  tabs.add(&pl->d_rdy, rdy);
+  tabs.add(&pl->d_kx2, pl->kx2);
+  tabs.add(&pl->d_kz2, pl->kz2);
   auto tof = [](const std::vector<double>& v) { return std::vector<float>(v.begin(), v.end()); };
-  if ((st = upload(pl, &pl->s_a, tof(pl->a))) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->s_c, tof(pl->c))) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->s_kx2, tof(pl->kx2))) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->s_kz2, tof(pl->kz2))) != CF_OK) return bail(st);
+  // FP64 tables of the transforms and stencils for FP64 plans, their FP32 copies
+  // for mixed ones (which form right-hand sides and residuals in FP64)
+  if (!fp64) {
+    tabs.add(&pl->s_a, tof(pl->a));
+    tabs.add(&pl->s_c, tof(pl->c));
+    tabs.add(&pl->s_kx2, tof(pl->kx2));
+    tabs.add(&pl->s_kz2, tof(pl->kz2));
+  }
   std::vector<cx<double>> twz(nz), twx(pl->nh), twp(pl->nh + 1);
   for (int m = 0; m < nz; ++m) twz[m] = unit_root(m, nz);
   for (int m = 0; m < pl->nh; ++m) twx[m] = unit_root(m, pl->nh);
@@ -1117,12 +1143,15 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     for (size_t i = 0; i < v.size(); ++i) o[i] = cf::mk((float)v[i].re, (float)v[i].im);
     return o;
   };
-  if ((st = upload(pl, &pl->tw_z64, twz)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->tw_x64, twx)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->twp64, twp)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->tw_z32, tofc(twz))) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->tw_x32, tofc(twx))) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->twp32, tofc(twp))) != CF_OK) return bail(st);
+  if (fp64) {
+    tabs.add(&pl->tw_z64, twz);
+    tabs.add(&pl->tw_x64, twx);
+    tabs.add(&pl->twp64, twp);
+  } else {
+    tabs.add(&pl->tw_z32, tofc(twz));
+    tabs.add(&pl->tw_x32, tofc(twx));
+    tabs.add(&pl->twp32, tofc(twp));
+  }
   if (opt.flags & CF_PLAN_Y_DCT) {
     std::vector<cx<double>> twy(ny), wqy(ny);
     for (int m = 0; m < ny; ++m) twy[m] = unit_root(m, ny);
@@ -1134,9 +1163,9 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
       const double sn = std::sin(M_PI * (double)m / (double)(2 * ny));
       lamy[m] = -(2.0 * sn / dyu) * (2.0 * sn / dyu);
     }
-    if ((st = upload(pl, &pl->tw_y64, twy)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_wqy, wqy)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_lamy, lamy)) != CF_OK) return bail(st);
+    tabs.add(&pl->tw_y64, twy);
+    tabs.add(&pl->d_wqy, wqy);
+    tabs.add(&pl->d_lamy, lamy);
   }
   {
     std::vector<double> rdyc(std::max(ny - 1, 1)), wl(std::max(ny - 1, 1)), wu(std::max(ny - 1, 1));
@@ -1145,14 +1174,7 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
       wl[j] = pl->dy[j + 1] / (pl->dy[j] + pl->dy[j + 1]);
       wu[j] = pl->dy[j] / (pl->dy[j] + pl->dy[j + 1]);
     }
-    if ((st = upload(pl, &pl->d_rdyc, rdyc)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_wl, wl)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_wu, wu)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_rdy, tof(rdy))) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_rdyc, tof(rdyc))) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_wl, tof(wl))) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_wu, tof(wu))) != CF_OK) return bail(st);
-    const double rdx = 1.0 / pl->dx, rdz = 1.0 / pl->dz;
+    tabs.add(&pl->d_rdyc, rdyc);
     std::vector<double> rows((size_t)(ny + 2 * cf::kRowPad) * 8, 0.0);
     for (int j = 0; j < ny; ++j) {
       double* r = rows.data() + (size_t)(j + cf::kRowPad) * 8;
@@ -1179,24 +1201,35 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
       r[6] = top || below ? 0.0 : rdyc[j];
       r[7] = j + 1 < ny - 1 ? rdyc[j + 1] : 0.0;
     }
-    if ((st = upload(pl, &pl->d_arows, arows)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_arows, tof(arows))) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_rows, rows)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_rows, tof(rows))) != CF_OK) return bail(st);
-    pl->g64 = cf::Geo<double>{pl->d_rdy, pl->d_rdyc, pl->d_wl, pl->d_wu, rdx, rdz, rdx * rdx, rdz * rdz,
-                              0.25 * rdx, 0.25 * rdz, nx, ny, nz, pl->d_rows + cf::kRowPad * 8};
-    pl->g32 = cf::Geo<float>{pl->s_rdy, pl->s_rdyc, pl->s_wl, pl->s_wu, (float)rdx, (float)rdz,
-                             (float)(rdx * rdx), (float)(rdz * rdz), (float)(0.25 * rdx), (float)(0.25 * rdz),
-                             nx, ny, nz, pl->s_rows + cf::kRowPad * 8};
-    std::vector<double> dyc(std::max(ny - 1, 1), 1.0);
-    for (int j = 0; j + 1 < ny; ++j) dyc[j] = pl->dyc[j];
-    if ((st = upload(pl, &pl->d_dyc, dyc)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_dy, tof(pl->dy))) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->s_dyc, tof(dyc))) != CF_OK) return bail(st);
-    pl->a64 = cf::AdjGeo<double>{pl->g64, pl->d_dy, pl->d_dyc, pl->d_rdyc, 0.5 * rdx, 0.5 * rdz,
-                                 pl->d_arows + cf::kRowPad * 8};
-    pl->a32 = cf::AdjGeo<float>{pl->g32, pl->s_dy, pl->s_dyc, pl->s_rdyc, (float)(0.5 * rdx), (float)(0.5 * rdz),
-                                pl->s_arows + cf::kRowPad * 8};
+    if (fp64) {
+      tabs.add(&pl->d_rows, rows);
+      tabs.add(&pl->d_arows, arows);
+    } else {
+      tabs.add(&pl->s_dy, tof(pl->dy));
+      tabs.add(&pl->s_rdyc, tof(rdyc));
+      tabs.add(&pl->s_rows, tof(rows));
+      tabs.add(&pl->s_arows, tof(arows));
+    }
+    tabs.add(&pl->d_numflag, std::vector<int>(1, 0));
+    tabs.add(&pl->d_special, pl->special);
+    std::vector<double> al(pl->special.size() * (size_t)ny), rd(al.size()), cpv(al.size());
+    for (size_t l = 0; l < pl->special.size(); ++l)
+      special_factors(pl, pl->special[l], al.data() + l * ny, rd.data() + l * ny, cpv.data() + l * ny);
+    tabs.add(&pl->d_special_alpha, al);
+    tabs.add(&pl->d_special_rden, rd);
+    tabs.add(&pl->d_special_cp, cpv);
+    if ((st = tabs.commit(pl)) != CF_OK) return bail(st);
+    const double rdx = 1.0 / pl->dx, rdz = 1.0 / pl->dz;
+    if (fp64) {
+      pl->g64 = cf::Geo<double>{pl->d_rdyc, rdx, rdz, rdx * rdx, rdz * rdz, 0.25 * rdx, 0.25 * rdz, nx, ny, nz,
+                                pl->d_rows + cf::kRowPad * 8};
+      pl->a64 = cf::AdjGeo<double>{pl->g64, pl->d_dy, 0.5 * rdx, 0.5 * rdz, pl->d_arows + cf::kRowPad * 8};
+    } else {
+      pl->g32 = cf::Geo<float>{pl->s_rdyc, (float)rdx, (float)rdz, (float)(rdx * rdx), (float)(rdz * rdz),
+                               (float)(0.25 * rdx), (float)(0.25 * rdz), nx, ny, nz, pl->s_rows + cf::kRowPad * 8};
+      pl->a32 = cf::AdjGeo<float>{pl->g32, pl->s_dy, (float)(0.5 * rdx), (float)(0.5 * rdz),
+                                  pl->s_arows + cf::kRowPad * 8};
+    }
   }
   // Workspace.  Step plans: the stage-1 fields and the two spectral buffers
   // share one block (the stage-1 fields are dead while the pressure is solved);
@@ -1248,19 +1281,11 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     pl->psum_nzb = (nz + K - 1) / K;
     if ((st = dalloc(pl, &pl->d_psum, (size_t)ny * pl->psum_nzb)) != CF_OK) return bail(st);
   }
-  if ((st = upload(pl, &pl->d_numflag, std::vector<int>(1, 0))) != CF_OK) return bail(st);
-  // block lists of the partitioned solve (room for one line per block, the
-  // most any lines_per_block can need)
-  if ((st = dalloc(pl, &pl->d_blocks, (size_t)pl->nkx * nz)) != CF_OK) return bail(st);
-  if ((st = upload_blocks(pl)) != CF_OK) return bail(st);
-  if ((st = upload(pl, &pl->d_special, pl->special)) != CF_OK) return bail(st);
-  {
-    std::vector<double> al(pl->special.size() * (size_t)ny), rd(al.size()), cpv(al.size());
-    for (size_t l = 0; l < pl->special.size(); ++l)
-      special_factors(pl, pl->special[l], al.data() + l * ny, rd.data() + l * ny, cpv.data() + l * ny);
-    if ((st = upload(pl, &pl->d_special_alpha, al)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_special_rden, rd)) != CF_OK) return bail(st);
-    if ((st = upload(pl, &pl->d_special_cp, cpv)) != CF_OK) return bail(st);
+  // block lists of the partitioned solve, where some blocks may drop (room for
+  // one line per block, the most any lines_per_block can need)
+  if (!pl->exact_all) {
+    if ((st = dalloc(pl, &pl->d_blocks, (size_t)pl->nkx * nz)) != CF_OK) return bail(st);
+    if ((st = upload_blocks(pl)) != CF_OK) return bail(st);
   }
   if (tune && (st = tune_partitions(pl, (size_t)lds_max)) != CF_OK) return bail(st);
   *out = pl;

@@ -20,10 +20,7 @@ namespace cf {
 
 template <typename T>
 struct Geo {
-  const T* rdy;   // 1/dy_j, ny
   const T* rdyc;  // 1/dyc_{j+1/2}, ny-1
-  const T* wl;    // dy_{j+1}/(dy_j+dy_{j+1}), ny-1: weight of the lower cell
-  const T* wu;    // dy_j/(dy_j+dy_{j+1}), ny-1: weight of the upper cell
   T rdx, rdz, rdx2, rdz2;
   T rdxq, rdzq;   // rdx / 4, rdz / 4
   int nx, ny, nz;
