@@ -98,6 +98,21 @@ __device__ __forceinline__ void st_once(cx<T> v, cx<T>* a) {
     *a = v;
   }
 }
+
+// Orders the LDS accesses of a line's threads (TPL consecutive threads, a power
+// of two).  A line that lies within one wave needs no barrier: a wave's LDS
+// accesses execute in order, and only the compiler has to keep them so.  (Block
+// barriers held all waves of a block to the slowest at every exchange.)
+template <int TPL>
+__device__ __forceinline__ void line_sync() {
+  if constexpr (TPL <= 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
 #endif
 // Data size from which the stencils and corrections take non-temporal loads and
 // stores for the arrays they touch once: the 8 XCDs' L2s together (32 MiB).

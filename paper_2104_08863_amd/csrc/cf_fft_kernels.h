@@ -37,21 +37,6 @@ struct FftT {
 CF_HD constexpr int lpad(int e) { return e + (e >> 4); }
 constexpr int lpad_len(int n) { return n + (n >> 4); }
 
-// Orders the LDS accesses of a line's threads (TPL consecutive threads, a power
-// of two).  A line that lies within one wave needs no barrier: a wave's LDS
-// accesses execute in order, and only the compiler has to keep them so.  (Block
-// barriers held all waves of a block to the slowest at every exchange.)
-template <int TPL>
-__device__ __forceinline__ void line_sync() {
-  if constexpr (TPL <= 64) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
-
 // Runs passes PASS..np-1 on the registers x (pass PASS input order on entry,
 // last-pass output order on exit).  sl: this line's LDS (N slots).  Every
 // thread of the block must call this (it contains block barriers when a line

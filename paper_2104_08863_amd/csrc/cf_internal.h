@@ -131,7 +131,7 @@ int ysolve_default_lb(int P, int M, bool fp64);
 size_t ysolve_lds_needed(int nyp, int P, int LB, bool fp64);
 
 template <typename T>
-hipError_t launch_ysolve(const YLaunch& y, const cx<T>* fin, cx<T>* pout, const T* a, const T* c,
+hipError_t launch_ysolve(YLaunch y, const cx<T>* fin, cx<T>* pout, const T* a, const T* c,
                          const T* kx2, const T* kz2, hipStream_t s);
 
 // Whole-line FP64 Thomas on the special lines alone (next to the slab passes).

@@ -59,137 +59,176 @@ __host__ __device__ constexpr size_t ysolve_lds_bytes(int nyp, int P, int LB, bo
          (sizeof(cx<T>) * 4 + sizeof(T) * 4 + (drop ? sizeof(zrow3<T>) : sizeof(zrow<T>))) * size_t(P) * LB;
 }
 
-// FP64 Thomas on one whole line by one block of any size.  The plan gives the
-// line's elimination in solved form: row j of the forward sweep is x_j =
-// al_j x_{j-1} + f_j rd_j (al_j = -a_j / den_j, rd_j = 1 / den_j), row j of the
-// backward sweep x_j -= cp_j x_{j+1}, so a row of either sweep is one fused
-// multiply-add; threads 0 and 1 run the two chains of the real and the
-// imaginary part (the division form of the same sweeps took 18 us on a line of
-// 64 rows and 65 us on one of 256, which nothing hides on a small grid; this
-// one is part of the partitioned solve's launch and ends with it).  The k^2 = 0
-// line, solved with its top row left out, is made compatible first (dy-weighted
-// mean of the right-hand side removed) and shifted afterwards to zero
-// dy-weighted mean (or, for a correction solve given the block sums psum of the
-// pressure it corrects, to -sum_j dy_j sum(p_j) / sum_j dy_j, the line value of
-// the constant -mean_W(p)).  All sums are taken in an order that does not
-// depend on the block size.  Reads of fin precede writes of pout, which may
-// alias.  sm: special_lds_bytes(ny) bytes.
+// v of the lane that DPP control CTRL names (of the rows of 16 lanes in ROWS),
+// or old where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_get(double old, double v) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// The wave's prefix steps: within a row of 16 lanes the values 1, 2, 4 and 8
+// lanes below, then the last lane of the row below for the odd rows and that of
+// lane 31 for the upper half.  op<CTRL, ROWS>() runs once for each.
+#define CF_WAVE_PREFIX(op) \
+  op(0x111, 0xf);          \
+  op(0x112, 0xf);          \
+  op(0x114, 0xf);          \
+  op(0x118, 0xf);          \
+  op(0x142, 0xa);          \
+  op(0x143, 0xc)
+
+// Sum over the 64 lanes, in a fixed order.
+__device__ __forceinline__ double wave_sum(double v) {
+#define CF_STEP(CTRL, ROWS) v += lane_get<CTRL, ROWS>(0.0, v)
+  CF_WAVE_PREFIX(CF_STEP);
+#undef CF_STEP
+  return __shfl(v, 63);
+}
+
+// One sweep x_j = sg t_j x_{j -+ 1} + x_j over the n rows of the real and the
+// imaginary part by the 64 lanes of a wave, upwards or (DOWN) from the last row.
+// A lane holds R consecutive rows (R odd: no two lanes of a read share a bank):
+// it composes its rows' affine maps, the wave scans the 64 compositions, and
+// the lane runs its rows again from the value that enters them.
+template <bool DOWN>
+__device__ __forceinline__ void line_sweep(const double* t, double* fr, double* fi, int n, int R, double sg) {
+  const int lane = threadIdx.x, r0 = lane * R, r1 = min(r0 + R, n);
+  constexpr int C = 4;  // rows whose operands are read at once
+  double A = 1.0, xr = 0.0, xi = 0.0;
+  auto rows = [&](auto store) {
+    for (int r = r0; r < r1; r += C) {
+      double al[C], br[C], bi[C];
+#pragma unroll
+      for (int u = 0; u < C; ++u) {
+        const int q = min(r + u, n - 1), j = DOWN ? n - 1 - q : q;
+        al[u] = sg * t[j];
+        br[u] = fr[j];
+        bi[u] = fi[j];
+      }
+#pragma unroll
+      for (int u = 0; u < C; ++u)
+        if (r + u < r1) {
+          xr = __builtin_fma(al[u], xr, br[u]);
+          xi = __builtin_fma(al[u], xi, bi[u]);
+          if constexpr (store) {
+            const int j = DOWN ? n - 1 - (r + u) : r + u;
+            fr[j] = xr;
+            fi[j] = xi;
+          } else {
+            A *= al[u];
+          }
+        }
+    }
+  };
+  rows(std::false_type{});
+#define CF_STEP(CTRL, ROWS)                                                          \
+  do {                                                                               \
+    const double ea = lane_get<CTRL, ROWS>(1.0, A), er = lane_get<CTRL, ROWS>(0.0, xr), \
+                 ei = lane_get<CTRL, ROWS>(0.0, xi);                                 \
+    xr = __builtin_fma(A, er, xr);                                                   \
+    xi = __builtin_fma(A, ei, xi);                                                   \
+    A *= ea;                                                                         \
+  } while (0)
+  CF_WAVE_PREFIX(CF_STEP);
+#undef CF_STEP
+  xr = __shfl_up(xr, 1);
+  xi = __shfl_up(xi, 1);
+  if (lane == 0) xr = xi = 0.0;
+  rows(std::true_type{});
+  line_sync<64>();
+}
+
+// FP64 Thomas on one whole line by the first wave of a block of at least one
+// wave.  The plan gives the line's elimination in solved form: row j of the
+// forward sweep is x_j = al_j x_{j-1} + f_j rd_j (al_j = -a_j / den_j, rd_j =
+// 1 / den_j), row j of the backward sweep x_j -= cp_j x_{j+1}, so both sweeps
+// are affine recurrences, which the wave scans (line_sweep).  Nothing hides
+// this line on a small grid: it is part of the partitioned solve's launch, which
+// ends with it (as two chains of dependent multiply-adds with block-wide tree sums
+// of the means, the solve of a 64 x ny x 64 grid took 10.0 / 15.9 / 27.6 us at ny =
+// 64 / 128 / 256, scanned 8.2 / 8.1 / 9.6; 128 x 512 x 64 mixed 52.1 -> 13.3).
+// The k^2 = 0 line, solved with its top row left out, is made compatible first
+// (dy-weighted mean of the right-hand side removed) and shifted afterwards to
+// zero dy-weighted mean (or, for a correction solve given the block sums psum of
+// the pressure it corrects, to -sum_j dy_j sum(p_j) / sum_j dy_j, the line value
+// of the constant -mean_W(p)).  All sums are taken in an order that does not
+// depend on the block size.  Reads of fin precede writes of pout, which may alias.
+// sm: special_lds_bytes(ny) bytes.
 template <typename T>
 __device__ __forceinline__ void special_line(const SpecialLines& sp, int l, const cx<T>* fin, cx<T>* pout, int ny,
                                              int nz, double* sm) {
   double* fr = sm;
   double* fi = fr + ny;
   double* sa = fi + ny;
-  double* sd = sa + ny;
-  double* sc = sd + ny;
-  double* red = sc + ny;  // kSpecialRed doubles
-  const long line = sp.lines[l];
-  const int kx = int(line / nz), kz = int(line % nz);
-  const long base = (long)kx * ny * nz + kz;
-  const bool mean_line = (kx == 0 && kz == 0);
+  double* sc = sa + ny;
+  double* sd = sc + ny;
+  double* red = sd + ny;  // kSpecialRed doubles
+  const int line = l > 0 ? sp.lines[l] : 0;  // line 0 is always the kx = kz = 0 line
+  const bool mean_line = line == 0;
+  const long base = (long)(line / nz) * ny * nz + line % nz;
   const int tid = threadIdx.x, nt = blockDim.x;
-  for (int j = tid; j < ny; j += nt) {
-    const cx<T> f = fin[base + (long)j * nz];
-    const double rd = sp.rden[(long)l * ny + j];
-    sa[j] = sp.alpha[(long)l * ny + j];
-    sc[j] = sp.cp[(long)l * ny + j];
-    sd[j] = mean_line ? rd : sp.dy[j];
-    fr[j] = mean_line ? double(f.re) : double(f.re) * rd;
-    fi[j] = mean_line ? double(f.im) : double(f.im) * rd;
-  }
-  __syncthreads();
-  // A non-finite value anywhere in a plane of the right-hand side reaches that
-  // plane's row of the kx = kz = 0 line (the sum over the plane): flag it for
-  // cf_plan_numeric_status.
-  if (mean_line && sp.numflag) {
+  double wsum = 0.0;
+  if (tid < 64) {
+    double sr = 0.0, si = 0.0;
     bool bad = false;
-    for (int j = tid; j < ny; j += nt) bad = bad || !__builtin_isfinite(fr[j]) || !__builtin_isfinite(fi[j]);
-    if (bad) *sp.numflag = 1;
-  }
-  // tree sums of `groups` runs of `width` partial sums in red
-  auto tree = [&](int groups, int width) {
-    for (int h = width / 2; h > 0; h /= 2) {
-      __syncthreads();
-      for (int e = tid; e < groups * h; e += nt) red[(e / h) * width + e % h] += red[(e / h) * width + h + e % h];
+#pragma unroll 4
+    for (int j = tid; j < ny; j += 64) {
+      const cx<T> f = fin[base + (long)j * nz];
+      const double rd = sp.rden[(long)l * ny + j], dy = sp.dy[j];
+      sa[j] = sp.alpha[(long)l * ny + j];  // 0 for j = 0, cp 0 for the last row: each sweep starts by itself
+      sc[j] = sp.cp[(long)l * ny + j];
+      sd[j] = rd;
+      fr[j] = f.re;
+      fi[j] = f.im;
+      sr = __builtin_fma(dy, double(f.re), sr);
+      si = __builtin_fma(dy, double(f.im), si);
+      wsum += dy;
+      bad = bad || !__builtin_isfinite(f.re) || !__builtin_isfinite(f.im);
     }
-    __syncthreads();
-  };
-  // dy-weighted means of the line, used by the k^2 = 0 line only
-  auto wmean = [&](double& mr, double& mi) {
-    for (int q = tid; q < 64; q += nt) {
-      double r = 0.0, im = 0.0, w = 0.0;
-      for (int j = q; j < ny; j += 64) {
-        const double d = sp.dy[j];
-        r += d * fr[j];
-        im += d * fi[j];
-        w += d;
-      }
-      red[q] = r;
-      red[64 + q] = im;
-      red[128 + q] = w;
+    // A non-finite value anywhere in a plane of the right-hand side reaches that
+    // plane's row of the kx = kz = 0 line (the sum over the plane): flag it for
+    // cf_plan_numeric_status.
+    if (mean_line && bad && sp.numflag) *sp.numflag = 1;
+    double mr = 0.0, mi = 0.0;
+    if (mean_line) {
+      wsum = wave_sum(wsum);
+      mr = wave_sum(sr) / wsum;
+      mi = wave_sum(si) / wsum;
     }
-    tree(3, 64);
-    mr = red[0] / red[128];
-    mi = red[64] / red[128];
-    __syncthreads();
-  };
-  if (mean_line) {
-    double mr, mi;
-    wmean(mr, mi);
-    for (int j = tid; j < ny; j += nt) {
+#pragma unroll 4
+    for (int j = tid; j < ny; j += 64) {
       fr[j] = (fr[j] - mr) * sd[j];
       fi[j] = (fi[j] - mi) * sd[j];
     }
-    __syncthreads();
-  }
-  const int n = mean_line ? ny - 1 : ny;
-  for (int part = tid; part < 2; part += nt) {
-    double* x = part == 0 ? fr : fi;
-    // sweeps in chunks of C rows; a chunk's operands are read while the chain
-    // of the chunk before runs
-    constexpr int C = 8;
-    double al[C], be[C], na[C], nb[C];
-    double xj = x[0];
-    auto fetch = [&](const double* t, int j0, int dir, double* a_, double* b_) {
-#pragma unroll
-      for (int u = 0; u < C; ++u) {
-        const int j = min(max(j0 + dir * u, 0), n - 1);
-        a_[u] = t[j];
-        b_[u] = x[j];
+    line_sync<64>();
+    const int n = mean_line ? ny - 1 : ny;
+    const int R = ((n + 63) / 64) | 1;
+    line_sweep<false>(sa, fr, fi, n, R, 1.0);
+    line_sweep<true>(sc, fr, fi, n, R, -1.0);
+    if (mean_line) {
+      if (tid == 0) fr[ny - 1] = fi[ny - 1] = 0.0;
+      sr = si = 0.0;
+#pragma unroll 4
+      for (int j = tid; j < n; j += 64) {
+        const double dy = sp.dy[j];
+        sr = __builtin_fma(dy, fr[j], sr);
+        si = __builtin_fma(dy, fi[j], si);
       }
-    };
-    fetch(sa, 1, 1, al, be);
-    for (int j0 = 1; j0 < n; j0 += C) {
-      fetch(sa, j0 + C, 1, na, nb);
-#pragma unroll
-      for (int u = 0; u < C; ++u)
-        if (j0 + u < n) {
-          xj = __builtin_fma(al[u], xj, be[u]);
-          x[j0 + u] = xj;
-        }
-#pragma unroll
-      for (int u = 0; u < C; ++u) al[u] = na[u], be[u] = nb[u];
+      mr = wave_sum(sr) / wsum;
+      mi = wave_sum(si) / wsum;
     }
-    fetch(sc, n - 2, -1, al, be);
-    for (int j0 = n - 2; j0 >= 0; j0 -= C) {
-      fetch(sc, j0 - C, -1, na, nb);
-#pragma unroll
-      for (int u = 0; u < C; ++u)
-        if (j0 - u >= 0) {
-          xj = __builtin_fma(-al[u], xj, be[u]);
-          x[j0 - u] = xj;
-        }
-#pragma unroll
-      for (int u = 0; u < C; ++u) al[u] = na[u], be[u] = nb[u];
+    if (tid == 0) {
+      red[0] = mr;
+      red[1] = mi;
     }
-    if (mean_line) x[ny - 1] = 0.0;
   }
   __syncthreads();
-  double orr = 0.0, oi = 0.0;
-  if (mean_line) wmean(orr, oi);
+  double orr = red[0];
+  const double oi = red[1];
   if (mean_line && sp.psum) {
-    // sum_j dy_j sum_b psum[j][b] / sum_j dy_j (the weights' sum is in red[128])
-    const double wsum = red[128];
+    // sum_j dy_j sum_b psum[j][b] / sum_j dy_j
     __syncthreads();
     for (int q = tid; q < kSpecialRed; q += nt) {
       double s = 0.0;
@@ -197,8 +236,13 @@ __device__ __forceinline__ void special_line(const SpecialLines& sp, int l, cons
       for (int e = q; e < ny * sp.nzb; e += kSpecialRed) s += sp.dy[e / sp.nzb] * sp.psum[e];
       red[q] = s;
     }
-    tree(1, kSpecialRed);
-    orr += red[0] / wsum;
+    for (int h = kSpecialRed / 2; h > 0; h /= 2) {
+      __syncthreads();
+      for (int e = tid; e < h; e += nt) red[e] += red[e + h];
+    }
+    if (tid == 0) red[0] /= wsum;
+    __syncthreads();
+    orr += red[0];
   }
   for (int j = tid; j < ny; j += nt) pout[base + (long)j * nz] = mk(T(fr[j] - orr), T(fi[j] - oi));
 }

@@ -101,7 +101,7 @@ static hipError_t ysolve_m(const YLaunch& y, const YArgs& ya, int threads, const
 }
 
 template <typename T>
-hipError_t launch_ysolve(const YLaunch& y, const cx<T>* fin, cx<T>* pout, const T* a, const T* c,
+hipError_t launch_ysolve(YLaunch y, const cx<T>* fin, cx<T>* pout, const T* a, const T* c,
                          const T* kx2, const T* kz2, hipStream_t s) {
   YArgs ya;
   ya.ny = y.ny;
@@ -127,6 +127,14 @@ hipError_t launch_ysolve(const YLaunch& y, const cx<T>* fin, cx<T>* pout, const 
     while (2 * ya.LB * np <= 256) ya.LB *= 2;
   }
   const int threads = ya.LB * (y.mode == kSlabLocal ? ya.pb - ya.pa : y.P);
+  // A special line needs a whole wave; beside smaller blocks the lines get a
+  // launch of their own (the order does not matter: the other blocks discard
+  // what they read of these lines).
+  if (threads < 64 && y.special.n > 0) {
+    const hipError_t e = launch_special_lines<T>(fin, pout, y.special, y.ny, y.nz, s);
+    if (e != hipSuccess) return e;
+    y.special = SpecialLines{};
+  }
   switch (y.M) {
 #define CF_CASE(M) \
   case M:          \
@@ -164,7 +172,7 @@ hipError_t launch_special_lines(const cx<T>* fin, cx<T>* pout, const SpecialLine
 }
 
 #define CF_INST(T)                                                                                  \
-  template hipError_t launch_ysolve<T>(const YLaunch&, const cx<T>*, cx<T>*, const T*, const T*,   \
+  template hipError_t launch_ysolve<T>(YLaunch, const cx<T>*, cx<T>*, const T*, const T*,   \
                                        const T*, const T*, hipStream_t);                           \
   template hipError_t launch_special_lines<T>(const cx<T>*, cx<T>*, const SpecialLines&, int, int, hipStream_t);
 CF_INST(double)
