@@ -303,26 +303,33 @@ k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {
 
 // g* = g - W G phi (weighted correction of the projection transpose);
 // W = dy_j for u and w, dyc_j for v (so the v part is g - (phi_{j+1} - phi_j)).
+// Pairs and planes as in k_correct.
 template <typename T, bool NT>
 __global__ void __launch_bounds__(256)
 k_correct_w(const T* __restrict__ gu, const T* __restrict__ gv, const T* __restrict__ gw, T* ou, T* ov, T* ow,
             const double* __restrict__ phi, AdjGeo<T> G) {
   const Geo<T>& g = G.g;
-  const long n = (long)g.nx * g.ny * g.nz;
-  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= n) return;
-  const int i = int(id % g.nx);
-  const long jk = id / g.nx;
-  const int k = int(jk % g.nz);
-  const int j = int(jk / g.nz);
-  const int ip = (i + 1 == g.nx) ? 0 : i + 1;
-  const int kp = (k + 1 == g.nz) ? 0 : k + 1;
-  const double p0 = phi[id];
+  const unsigned nh = g.nx / 2, m = blockIdx.x * blockDim.x + threadIdx.x;
+  if (m >= nh * g.nz) return;
+  const int j = blockIdx.y, k = int(m / nh), i = int(m - k * nh), kp = (k + 1 == g.nz) ? 0 : k + 1;
+  const long row = (long)j * g.nz + k, id = row * nh + i;
+  const cx<double>* p2 = reinterpret_cast<const cx<double>*>(phi);
+  const cx<double> p0 = p2[id], pk = p2[((long)j * g.nz + kp) * nh + i];
+  const double pn = phi[row * g.nx + (2 * i + 2 == g.nx ? 0 : 2 * i + 2)];
   const T dyj = G.dy[j];
+  auto in = [&](const T* a) { return ld_once<NT>(reinterpret_cast<const cx<T>*>(a) + id); };
+  auto out = [&](T* a, T r0, T r1) { st_once<NT>(mk(r0, r1), reinterpret_cast<cx<T>*>(a) + id); };
   // g and g* are touched once (streamed when NT, as in the forward correction)
-  st_once<NT>(ld_once<NT>(&gu[id]) - dyj * (T(phi[jk * g.nx + ip] - p0) * g.rdx), &ou[id]);
-  st_once<NT>(ld_once<NT>(&gw[id]) - dyj * (T(phi[((long)j * g.nz + kp) * g.nx + i] - p0) * g.rdz), &ow[id]);
-  st_once<NT>((j == g.ny - 1) ? T(0) : ld_once<NT>(&gv[id]) - T(phi[id + (long)g.nz * g.nx] - p0), &ov[id]);
+  const cx<T> a = in(gu), c = in(gw);
+  out(ou, a.re - dyj * (T(p0.im - p0.re) * g.rdx), a.im - dyj * (T(pn - p0.im) * g.rdx));
+  out(ow, c.re - dyj * (T(pk.re - p0.re) * g.rdz), c.im - dyj * (T(pk.im - p0.im) * g.rdz));
+  cx<T> b = mk(T(0), T(0));
+  if (j != g.ny - 1) {
+    const cx<double> pj = p2[id + (long)g.nz * nh];
+    b = in(gv);
+    b = mk(b.re - T(pj.re - p0.re), b.im - T(pj.im - p0.im));
+  }
+  out(ov, b.re, b.im);
 }
 
 }  // namespace cf

@@ -282,46 +282,52 @@ k_rk_stage(const T* __restrict__ u, const T* __restrict__ v, const T* __restrict
 #undef CF_RK_STORE
 }
 
-// u1 = us - dt G p at point id = (j, k, i), row = (j nz + k) nx (in place; the
-// top-wall v plane is 0); returns the corrected values.  Each velocity value
-// is read and written once, non-temporally when NT (the FP64 correction on
-// 1024x256x512 runs 5 % faster than with plain loads and stores); p, whose
-// values neighbouring points share, is read through the caches.
+// u1 = us - dt G p at the points 2i and 2i + 1 of row (j, k) (in place; the
+// top-wall v plane is 0); returns the corrected values.  Two neighbours in x take
+// one load and store per array (rows have an even length and the arrays are
+// 16-byte aligned).  Each velocity value is read and written once,
+// non-temporally when NT (the FP64 correction on 1024x256x512 runs 5 % faster
+// than with plain loads and stores); p, whose values neighbouring points share,
+// is read through the caches.
 template <bool NT, typename T>
-__device__ __forceinline__ void correct_point(T* u, T* v, T* w, const double* __restrict__ p, const Geo<T>& g,
-                                              T dt, long id, long row, int i, int k, int j, T& cu, T& cv, T& cw) {
-  const int ip = (i + 1 == g.nx) ? 0 : i + 1;
-  const int kp = (k + 1 == g.nz) ? 0 : k + 1;
-  const double p0 = p[id];
-  const T gx = T(p[row + ip] - p0) * g.rdx;
-  const T gz = T(p[((long)j * g.nz + kp) * g.nx + i] - p0) * g.rdz;
-  cu = ld_once<NT>(&u[id]) - dt * gx;
-  st_once<NT>(cu, &u[id]);
-  cw = ld_once<NT>(&w[id]) - dt * gz;
-  st_once<NT>(cw, &w[id]);
-  if (j == g.ny - 1) {
-    cv = T(0);
-  } else {
-    const T gy = T(p[id + (long)g.nz * g.nx] - p0) * g.rdyc[j];
-    cv = ld_once<NT>(&v[id]) - dt * gy;
+__device__ __forceinline__ void correct_pair(T* u, T* v, T* w, const double* __restrict__ p, const Geo<T>& g, T dt,
+                                             int i, int k, int j, cx<T>& cu, cx<T>& cv, cx<T>& cw) {
+  const int nh = g.nx / 2, kp = (k + 1 == g.nz) ? 0 : k + 1;
+  const long row = (long)j * g.nz + k, id = row * nh + i;
+  const cx<double>* p2 = reinterpret_cast<const cx<double>*>(p);
+  const cx<double> p0 = p2[id], pk = p2[((long)j * g.nz + kp) * nh + i];
+  const double pn = p[row * g.nx + (2 * i + 2 == g.nx ? 0 : 2 * i + 2)];
+  cx<T>*u2 = reinterpret_cast<cx<T>*>(u) + id, *v2 = reinterpret_cast<cx<T>*>(v) + id,
+       *w2 = reinterpret_cast<cx<T>*>(w) + id;
+  cu = ld_once<NT>(u2);
+  cw = ld_once<NT>(w2);
+  cu = mk(cu.re - dt * (T(p0.im - p0.re) * g.rdx), cu.im - dt * (T(pn - p0.im) * g.rdx));
+  cw = mk(cw.re - dt * (T(pk.re - p0.re) * g.rdz), cw.im - dt * (T(pk.im - p0.im) * g.rdz));
+  st_once<NT>(cu, u2);
+  st_once<NT>(cw, w2);
+  cv = mk(T(0), T(0));
+  if (j != g.ny - 1) {
+    const cx<double> pj = p2[id + (long)g.nz * nh];
+    cv = ld_once<NT>(v2);
+    cv = mk(cv.re - dt * (T(pj.re - p0.re) * g.rdyc[j]), cv.im - dt * (T(pj.im - p0.im) * g.rdyc[j]));
   }
-  st_once<NT>(cv, &v[id]);
+  st_once<NT>(cv, v2);
 }
 
-// u1 = us - dt G p (in place on the velocity arrays); the top-wall v plane is 0.
-// One thread per point; the neighbours of p come through the caches.
+// u1 = us - dt G p, one thread per pair.  Memory-bound: six velocity passes and
+// one of p.  A grid row of blocks holds one plane, so that a thread's indices
+// take one 32-bit division.  Against one point per thread of the whole grid:
+// FP64 1024x256x512 1.274 -> 1.271 ms (5.9 TB/s), 256x128x256 81 -> 74 us, FP32
+// 512x192x512 338 -> 306 us (5.3 TB/s); of the scalar form with the plane's grid
+// the last took 333.
 template <typename T, bool NT>
 __global__ void __launch_bounds__(256)
 k_correct(T* u, T* v, T* w, const double* __restrict__ p, Geo<T> g, T dt) {
-  const long n = (long)g.nx * g.ny * g.nz;
-  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= n) return;
-  const int i = int(id % g.nx);
-  const long jk = id / g.nx;
-  const int k = int(jk % g.nz);
-  const int j = int(jk / g.nz);
-  T cu, cv, cw;
-  correct_point<NT, T>(u, v, w, p, g, dt, id, jk * g.nx, i, k, j, cu, cv, cw);
+  const unsigned nh = g.nx / 2, m = blockIdx.x * blockDim.x + threadIdx.x;  // pair of plane j
+  if (m >= nh * g.nz) return;
+  const int k = int(m / nh);
+  cx<T> cu, cv, cw;
+  correct_pair<NT, T>(u, v, w, p, g, dt, int(m - k * nh), k, blockIdx.y, cu, cv, cw);
 }
 
 // Block reduction of six FP64 per-thread sums in a fixed order (wave shuffles,
@@ -352,24 +358,22 @@ __global__ void __launch_bounds__(TH)
 k_correct_stats(T* __restrict__ u, T* __restrict__ v, T* __restrict__ w, const double* __restrict__ p, Geo<T> g,
                 T dt, double* __restrict__ part, int nch) {
   __shared__ double red[6][TH / 64];
-  const int nxz = g.nx * g.nz;
+  const int nh = g.nx / 2, n2 = nh * g.nz;  // pairs of a plane
   const int j = blockIdx.x / nch, c = blockIdx.x % nch;
-  const int len = (nxz + nch - 1) / nch;
-  const int e0 = c * len, e1 = (e0 + len < nxz) ? e0 + len : nxz;
-  const long o = (long)j * nxz;
+  const int len = (n2 + nch - 1) / nch;
+  const int e0 = c * len, e1 = (e0 + len < n2) ? e0 + len : n2;
   double sm[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
+#pragma unroll 2
   for (int e = e0 + threadIdx.x; e < e1; e += TH) {
-    const int i = e % g.nx, k = e / g.nx;
-    T cu, cv, cw;
-    correct_point<NT, T>(u, v, w, p, g, dt, o + e, o + e - i, i, k, j, cu, cv, cw);
-    const double a = double(cu), b = double(cv), d = double(cw);
-    sm[0] += a;
-    sm[1] += b;
-    sm[2] += d;
-    sm[3] += a * a;
-    sm[4] += b * b;
-    sm[5] += d * d;
+    const int k = e / nh;
+    cx<T> cu, cv, cw;
+    correct_pair<NT, T>(u, v, w, p, g, dt, e - k * nh, k, j, cu, cv, cw);
+    const double q[6] = {double(cu.re), double(cv.re), double(cw.re), double(cu.im), double(cv.im), double(cw.im)};
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      sm[f % 3] += q[f];
+      sm[f % 3 + 3] += q[f] * q[f];
+    }
   }
   const double x = block_sum6<TH>(sm, red);
   if (threadIdx.x < 6) part[(long)blockIdx.x * 6 + threadIdx.x] = x;

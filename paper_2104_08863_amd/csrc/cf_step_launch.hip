@@ -71,11 +71,11 @@ template <typename T>
 hipError_t launch_correct(T* u, T* v, T* w, const double* p, const Geo<T>& g, T dt, hipStream_t s) {
   const long n = (long)g.nx * g.ny * g.nz;
   const int th = 256;
-  const long blocks = (n + th - 1) / th;
+  const dim3 blocks((g.nx / 2 * g.nz + th - 1) / th, g.ny);
   if (n * (long)sizeof(T) >= kStreamBytes)
-    hipLaunchKernelGGL((k_correct<T, true>), dim3(blocks), dim3(th), 0, s, u, v, w, p, g, dt);
+    hipLaunchKernelGGL((k_correct<T, true>), blocks, dim3(th), 0, s, u, v, w, p, g, dt);
   else
-    hipLaunchKernelGGL((k_correct<T, false>), dim3(blocks), dim3(th), 0, s, u, v, w, p, g, dt);
+    hipLaunchKernelGGL((k_correct<T, false>), blocks, dim3(th), 0, s, u, v, w, p, g, dt);
   return hipGetLastError();
 }
 
