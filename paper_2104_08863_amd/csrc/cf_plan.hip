@@ -182,6 +182,7 @@ struct cf_plan {
     double* p;
     double* acc;
     double dt, nu, fx;
+    int steps;  // 1: a to b; 2: a to b and back to a
     hipGraphExec_t exec;
     unsigned long long last_use;
   };
@@ -227,7 +228,8 @@ cf_status upload(cf_plan* pl, T** out, const std::vector<T>& h) {
 }
 
 // Device tables collected during plan creation and placed by one allocation and
-// one copy (each of its own cost 20-30 us of a plan's creation, 40 tables 1 ms).
+// one copy (each by itself, the FP64 step plan of 192x130x96 took 733 us to
+// create; 233 now).
 struct Tables {
   std::vector<unsigned char> bytes;
   std::vector<std::pair<void**, size_t>> slots;
@@ -1529,10 +1531,11 @@ cf_status loop_step(cf_plan* pl, void* const a[3], void* const b[3], double* p, 
 
 // Records loop_step into an executable graph on the plan's capture stream.
 cf_status record_step(cf_plan* pl, void* const a[3], void* const b[3], double* p, double dt, double nu, double fx,
-                      double* acc, hipGraphExec_t* out) {
+                      double* acc, int steps, hipGraphExec_t* out) {
   hipStream_t g = pl->gstream;
   CF_HIP(hipStreamBeginCapture(g, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-  const cf_status st = loop_step(pl, a, b, p, dt, nu, fx, acc, g);
+  cf_status st = loop_step(pl, a, b, p, dt, nu, fx, acc, g);
+  if (st == CF_OK && steps == 2) st = loop_step(pl, b, a, p, dt, nu, fx, nullptr, g);
   hipGraph_t graph = nullptr;
   const hipError_t e = hipStreamEndCapture(g, &graph);
   if (st != CF_OK) {
@@ -1580,29 +1583,37 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
     return CF_OK;
   }
   if (nsteps == 0) return CF_OK;
-  // One recorded step per (parity, statistics or not), found in or added to
-  // the plan's cache (at most kMaxGraphs entries; the least recently used one
-  // is dropped after the capture stream has drained).  Per-launch event timing
+  // Recorded by (parity, kind): one step, one step with statistics, or two steps
+  // without (the device starts a graph later than a kernel in a stream: a 64^3
+  // step of 48 us takes 56.5 from graphs of one step, 54.5 from graphs of two, and
+  // 20 steps with statistics every 5 went 1204 -> 1155 us; longer graphs would
+  // cost a first call more to record).  Found in or added to the plan's cache (at
+  // most kMaxGraphs entries; the least recently used one is dropped after the
+  // capture stream has drained).  Per-launch event timing
   // is not recorded into graphs.
   constexpr size_t kMaxGraphs = 8;
-  auto find = [&](void* const* a, void* const* b, double* acc) -> hipGraphExec_t {
+  enum { kOne, kStats, kTwo, kKinds };
+  auto kind_at = [&](int k) { return acc_at(k) ? kStats : k + 1 < nsteps && !acc_at(k + 1) ? kTwo : kOne; };
+  auto find = [&](void* const* a, void* const* b, double* acc, int steps) -> hipGraphExec_t {
     for (auto& g : pl->graphs)
       if (g.a[0] == a[0] && g.a[1] == a[1] && g.a[2] == a[2] && g.b[0] == b[0] && g.b[1] == b[1] &&
-          g.b[2] == b[2] && g.p == p && g.acc == acc && g.dt == dt && g.nu == nu && g.fx == fx) {
+          g.b[2] == b[2] && g.p == p && g.acc == acc && g.dt == dt && g.nu == nu && g.fx == fx &&
+          g.steps == steps) {
         g.last_use = ++pl->graph_clock;
         return g.exec;
       }
     return nullptr;
   };
-  hipGraphExec_t ex[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
-  for (int k = 0; k < nsteps && k < 2 * (stats_every > 0 ? stats_every : 1); ++k) {
-    const int par = k & 1, ws = acc_at(k) ? 1 : 0;
-    if (ex[par][ws]) continue;
+  hipGraphExec_t ex[2][kKinds] = {};
+  for (int k = 0, steps; k < nsteps; k += steps) {
+    const int par = k & 1, kind = kind_at(k);
+    steps = kind == kTwo ? 2 : 1;
+    if (ex[par][kind]) continue;
     void* const* a = par ? B : A;
     void* const* b = par ? A : B;
-    double* acc = ws ? stats_acc : nullptr;
-    ex[par][ws] = find(a, b, acc);
-    if (ex[par][ws]) continue;
+    double* acc = kind == kStats ? stats_acc : nullptr;
+    ex[par][kind] = find(a, b, acc, steps);
+    if (ex[par][kind]) continue;
     if (pl->graphs.size() >= kMaxGraphs) {
       CF_HIP(hipStreamSynchronize(pl->gstream), "hipStreamSynchronize");
       size_t old = 0;
@@ -1619,7 +1630,7 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
     const bool timing = pl->timing;
     pl->timing = false;
     hipGraphExec_t g = nullptr;
-    const cf_status st = record_step(pl, a, b, p, dt, nu, fx, acc, &g);
+    const cf_status st = record_step(pl, a, b, p, dt, nu, fx, acc, steps, &g);
     pl->timing = timing;
     CF_TRY(st);
     cf_plan::GraphEntry en;
@@ -1632,14 +1643,16 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
     en.dt = dt;
     en.nu = nu;
     en.fx = fx;
+    en.steps = steps;
     en.exec = g;
     en.last_use = ++pl->graph_clock;
     pl->graphs.push_back(en);
-    ex[par][ws] = g;
+    ex[par][kind] = g;
   }
   hipError_t e = hipEventRecord(pl->ev_gin, s);
   if (e == hipSuccess) e = hipStreamWaitEvent(pl->gstream, pl->ev_gin, 0);
-  for (int k = 0; k < nsteps && e == hipSuccess; ++k) e = hipGraphLaunch(ex[k & 1][acc_at(k) ? 1 : 0], pl->gstream);
+  for (int k = 0; k < nsteps && e == hipSuccess; k += kind_at(k) == kTwo ? 2 : 1)
+    e = hipGraphLaunch(ex[k & 1][kind_at(k)], pl->gstream);
   if (e == hipSuccess) e = hipEventRecord(pl->ev_gout, pl->gstream);
   if (e == hipSuccess) e = hipStreamWaitEvent(s, pl->ev_gout, 0);
   if (e != hipSuccess) return dev_fail(e, "graph replay");
