@@ -691,10 +691,12 @@ def slab_figures(steps):
 
 
 def drop_figures(steps):
-    """The wall-normal solve of the step grid with the default drop tolerance
-    (the dropped reduced system as an outer PDD of 4 groups of 4 partitions on
-    most lines) against the same plan with drop_tol = 0 (exact reduced system on
-    every line): mean y-solve kernel time of each, lines dropped."""
+    """The wall-normal solve of the step grid with a drop tolerance just above the
+    default (the dropped reduced system as an outer PDD of 4 groups of 4
+    partitions on most lines; at the default, the round-off of the precision, a
+    one-device plan solves every line exactly) against the same plan with drop_tol
+    = 0 (exact reduced system on every line): mean y-solve kernel time of each,
+    lines dropped."""
     import torch
 
     from paper_2104_08863_amd import synth
@@ -705,7 +707,7 @@ def drop_figures(steps):
     gen.manual_seed(0)
     res = {}
     fh = None
-    for tag, tol in (("dropped", -1.0), ("exact", 0.0)):
+    for tag, tol in (("dropped", 1.001e-15), ("exact", 0.0)):
         pl = Plan(wl.nx, wl.ny, wl.nz, wl.lx, wl.lz, wl.y_faces(), precision="fp64", drop_tol=tol)
         if fh is None:
             fh = torch.randn(pl.nkx, wl.ny, wl.nz, dtype=torch.complex128, device=dev, generator=gen)
