@@ -234,8 +234,8 @@ cf_status cf_plane_stats(cf_plan* plan, const void* u, const void* v, const void
  * (ny, nz, nx) receiving the last step's pressure, or NULL.
  * use_graph != 0 replays the steps from HIP graphs on a plan-owned stream
  * (ordered after earlier work on `stream`, and later work on `stream` after
- * it): one recorded step per parity, with and without the statistics pass, kept
- * in the plan (up to 8, least recently used dropped) and reused by later calls
+ * it): one recorded step per parity, with and without the statistics pass, and
+ * two consecutive steps where neither takes statistics, kept in the plan (up to 8, least recently used dropped) and reused by later calls
  * with the same arrays and parameters, which removes the per-launch host cost.
  * Results are identical in both modes.
  * The plan must have been created with CF_PLAN_STEP.
