@@ -112,7 +112,8 @@ typedef struct {
   size_t workspace_bytes; /* device memory owned by the plan */
   int lines_per_block;    /* lines per block of the partitioned solve */
   size_t slab_iface_bytes; /* device bytes of the interface buffer of cf_solve_spectral_slabs:
-                              n_parts * 8 * n_lines values of the plan's precision */
+                              n_parts * 8 * n_lines values of the plan's precision (of
+                              the larger count where slabs may take another one) */
   int drop_parts;         /* G, the outer partitions of the dropped reduced system */
   long long n_dropped_lines; /* lines whose block of lines_per_block consecutive lines lies
                               wholly above k2_threshold: those the partitioned solve may drop
@@ -288,15 +289,19 @@ cf_status cf_solve_spectral(cf_plan* plan, const void* fhat, void* phat, void* s
  * across processes (Section 2.2 PDD; Section 3: each process owns a range of
  * partitions and exchanges only interface values).  The ny rows of every line
  * are cut into n_slabs slabs of n_parts / n_slabs partitions (n_slabs must
- * divide the plan's n_parts).  For every slab a local pass solves its
+ * divide the plan's n_parts; in a CF_FP64 plan with n_parts = 0 it may also
+ * divide the fewest partitions that divide ny, powers of two preferred, or, where
+ * none does, that pad it least: such slabs take partitions of that count and the
+ * exact reduced system).  For every slab a local pass solves its
  * partitions and writes their interface rows (x~_1, x~_M, v_1, v_M, w_1, w_M
  * per partition and line) into iface; then, for every slab, a finishing pass
  * reads all interface rows, solves the reduced system, redoes the slab's local
  * solves and writes the slab's corrected rows.  On several devices the slabs
  * would be the devices and iface the buffer they exchange; here the slabs run
  * one after another on one device.  The result equals cf_solve_spectral's
- * bitwise.  iface: device buffer of cf_plan_info.slab_iface_bytes (layout
- * [n_parts][8][n_lines], plan precision), overwritten.  phat may be fhat itself but
+ * bitwise (with partitions of another count than n_parts: to round-off).  iface:
+ * device buffer of cf_plan_info.slab_iface_bytes (layout
+ * [partitions][8][n_lines], plan precision), overwritten.  phat may be fhat itself but
  * must not overlap it otherwise (CF_ERR_ARG).
  * Not available with CF_PLAN_Y_DCT (no partitions).
  */
@@ -323,7 +328,7 @@ cf_status cf_plan_numeric_status(cf_plan* plan, void* stream);
  * array of the library (32 MiB; each device the library runs on holds its own
  * copy until the process ends, its address taken at plan creation).  The call
  * makes no device allocation and records no per-kernel timing.  Plans whose
- * interface rows (cf_plan_info.slab_iface_bytes) exceed 32 MiB are rejected
+ * interface rows (8 * n_lines values per partition) exceed 32 MiB are rejected
  * with CF_ERR_ARG before any work is enqueued.  Every call on a device shares
  * that device's array: calls that overlap on one device (several streams, or
  * several host threads) race and must be serialised by the caller.  The array

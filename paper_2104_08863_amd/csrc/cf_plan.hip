@@ -98,6 +98,9 @@ struct cf_plan {
   int device;
   int P, M;
   int LB;  // lines per block of the partitioned solve
+  // partitions of the slab passes for slab counts that do not divide P (0: none,
+  // see even_parts)
+  int slab_P = 0;
   int G;   // outer partitions of the dropped reduced system
   double k2drop;
   long long n_drop;     // lines above the drop threshold
@@ -430,6 +433,19 @@ bool parts_ok(int ny, int P, bool fp64) {
   return cf::ysolve_m_compiled(M, fp64) && (P - 1) * M < ny;
 }
 
+// The fewest partitions that divide ny, preferring powers of two, else the
+// partitioning with the fewest padding rows (then the fewest partitions).
+int even_parts(int ny, bool fp64) {
+  for (int P = 1; P <= 64; P *= 2)
+    if (ny % P == 0 && parts_ok(ny, P, fp64)) return P;
+  for (int P = 1; P <= 64; ++P)
+    if (ny % P == 0 && parts_ok(ny, P, fp64)) return P;
+  int best = 0;
+  for (int P = 1; P <= 64; ++P)
+    if (parts_ok(ny, P, fp64) && (best == 0 || P * part_rows(ny, P) < best * part_rows(ny, best))) best = P;
+  return best;
+}
+
 // Automatic partition count.  FP64: the least rows * (1 + 16/M) over the
 // admissible P, rows = P*M: a partition costs its rows plus, for its share of
 // the reduced system, about as much as 16 rows (the order of the timings of
@@ -438,28 +454,19 @@ bool parts_ok(int ny, int P, bool fp64) {
 // instead of 54 us on 512x97x256 and 373 instead of 171 us on 512x341x256); a
 // power of two that divides ny keeps its place within 20 % of that, which the
 // timings do not tell apart (192 rows: 16 x 12 81 us, 12 x 16 83 us).  CF_MIXED:
-// the fewest partitions that divide ny, preferring powers of two, else the
-// fewest padding rows (another count rounds the FP32 solve differently).
+// even_parts (another count rounds the FP32 solve differently).
 int auto_parts(int ny, bool fp64) {
+  const int even = even_parts(ny, fp64);
+  if (!fp64) return even;
   auto cost = [ny](int P) {
     const int M = part_rows(ny, P);
     return double(P * M) * (1.0 + 16.0 / M);
   };
-  int pow2 = 0;
-  for (int P = 1; P <= 64 && pow2 == 0; P *= 2)
-    if (ny % P == 0 && parts_ok(ny, P, fp64)) pow2 = P;
-  if (!fp64) {
-    if (pow2) return pow2;
-    for (int P = 1; P <= 64; ++P)
-      if (ny % P == 0 && parts_ok(ny, P, fp64)) return P;
-  }
   int best = 0;
-  for (int P = 1; P <= 64; ++P) {
-    if (!parts_ok(ny, P, fp64)) continue;
-    const bool less = best == 0 || (fp64 ? cost(P) < cost(best) : P * part_rows(ny, P) < best * part_rows(ny, best));
-    if (less) best = P;
-  }
-  return pow2 && cost(pow2) <= 1.2 * cost(best) ? pow2 : best;
+  for (int P = 1; P <= 64; ++P)
+    if (parts_ok(ny, P, fp64) && (best == 0 || cost(P) < cost(best))) best = P;
+  const bool pow2 = even > 0 && (even & (even - 1)) == 0 && ny % even == 0;
+  return pow2 && cost(even) <= 1.2 * cost(best) ? even : best;
 }
 
 cf_status check_plan(const cf_plan* pl) {
@@ -592,19 +599,21 @@ cf::SpecialLines special_lines(const cf_plan* pl, const double* psum = nullptr) 
 
 // One launch of the partitioned line solve with the plan's partitioning (whole
 // lines, with the special lines given, or one slab's local or finishing pass
-// over partitions [pa, pb)).
+// over partitions [pa, pb)).  P: the plan's count, or its slab_P (slab passes;
+// every line then takes the exact reduced system).
 template <typename T>
 hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStream_t s,
                       const cf::SpecialLines& special = cf::SpecialLines{}, int mode = cf::kWhole, int pa = 0,
-                      int pb = 0, void* iface = nullptr) {
+                      int pb = 0, void* iface = nullptr, int P = 0) {
   using TB = Tabs<T>;
   cf::YLaunch y;
   y.ny = pl->ny;
   y.nz = pl->nz;
   y.nkx = pl->nkx;
-  y.P = pl->P;
-  y.M = pl->M;
-  y.LB = pl->LB;
+  const bool own = P == 0 || P == pl->P;
+  y.P = own ? pl->P : P;
+  y.M = own ? pl->M : part_rows(pl->ny, P);
+  y.LB = own ? pl->LB : 0;
   y.nlines = (long)pl->nkx * pl->nz;
   y.skip_kx = pl->mixed() ? pl->opt.fp64_kx : 0;
   y.skip_kz = pl->mixed() ? pl->opt.fp64_kz : 0;
@@ -612,9 +621,9 @@ hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStrea
   y.pa = pa;
   y.pb = pb;
   y.iface = iface;
-  y.G = pl->G;
+  y.G = own ? pl->G : P;
   y.special = special;
-  if (pl->d_blocks) {
+  if (own && pl->d_blocks) {
     y.blocks_exact = pl->d_blocks;
     y.n_exact = (long)pl->blocks_exact.size();
     y.blocks_drop = pl->blocks_drop.empty() ? nullptr : pl->d_blocks + pl->blocks_exact.size();
@@ -623,16 +632,32 @@ hipError_t pdd_launch(const cf_plan* pl, const cx<T>* fin, cx<T>* pout, hipStrea
   return cf::launch_ysolve<T>(y, fin, pout, TB::a(pl), TB::c(pl), TB::kx2(pl), TB::kz2(pl), s);
 }
 
+// Partitions of a solve in n_slabs y-slabs (0: none that n_slabs divides), and
+// the bytes of its interface rows.
+int slab_parts(const cf_plan* pl, int n_slabs) {
+  if (n_slabs < 1) return 0;
+  if (pl->P % n_slabs == 0) return pl->P;
+  return pl->slab_P > 0 && pl->slab_P % n_slabs == 0 ? pl->slab_P : 0;
+}
+size_t slab_bytes(const cf_plan* pl, int P) {
+  return (size_t)P * 8 * (size_t)pl->nkx * pl->nz * (pl->mixed() ? sizeof(float) : sizeof(double));
+}
+cf_status slab_refuse(const cf_plan* pl) {
+  std::string counts = std::to_string(pl->P);
+  if (pl->slab_P > 0) counts += " or " + std::to_string(pl->slab_P);
+  return fail(CF_ERR_ARG, "n_slabs must divide the plan's partition count " + counts);
+}
+
 // The partitioned solve as n_slabs y-slabs: every slab's local pass, then the
 // whole-line FP64 solves of the special lines on the side stream next to every
 // slab's finishing pass (they touch only the special lines, which the
 // finishing passes do not write).
 template <typename T>
 cf_status slabs_t(cf_plan* pl, int n_slabs, const cx<T>* fin, cx<T>* pout, void* iface, hipStream_t s) {
-  const int per = pl->P / n_slabs;
+  const int P = slab_parts(pl, n_slabs), per = P / n_slabs;
   for (int g = 0; g < n_slabs; ++g)
     CF_TRY(timed(pl, CF_K_SLAB_LOCAL, s, "slab local launch", [&] {
-      return pdd_launch<T>(pl, fin, pout, s, {}, cf::kSlabLocal, g * per, (g + 1) * per, iface);
+      return pdd_launch<T>(pl, fin, pout, s, {}, cf::kSlabLocal, g * per, (g + 1) * per, iface, P);
     }));
   CF_HIP(hipEventRecord(pl->ev_fork, s), "hipEventRecord");
   CF_HIP(hipStreamWaitEvent(pl->aux, pl->ev_fork, 0), "hipStreamWaitEvent");
@@ -642,7 +667,7 @@ cf_status slabs_t(cf_plan* pl, int n_slabs, const cx<T>* fin, cx<T>* pout, void*
   CF_HIP(hipEventRecord(pl->ev_join, pl->aux), "hipEventRecord");
   for (int g = 0; g < n_slabs; ++g)
     CF_TRY(timed(pl, CF_K_SLAB_FINISH, s, "slab finish launch", [&] {
-      return pdd_launch<T>(pl, fin, pout, s, {}, cf::kSlabFinish, g * per, (g + 1) * per, iface);
+      return pdd_launch<T>(pl, fin, pout, s, {}, cf::kSlabFinish, g * per, (g + 1) * per, iface, P);
     }));
   CF_HIP(hipStreamWaitEvent(s, pl->ev_join, 0), "hipStreamWaitEvent");
   return CF_OK;
@@ -1003,7 +1028,12 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     return fail(CF_ERR_ARG, "CF_PLAN_TUNE_PARTS needs n_parts = 0, lines_per_block = 0 and the partitioned solve");
   int P = opt.n_parts;
   const bool fp64 = opt.precision == CF_FP64;
-  if (P == 0) P = auto_parts(ny, fp64);
+  if (P == 0) {
+    // an explicit drop_parts that divides the even count alone keeps that count
+    const int even = even_parts(ny, fp64);
+    P = auto_parts(ny, fp64);
+    if (opt.drop_parts > 0 && P > 0 && P % opt.drop_parts != 0 && even % opt.drop_parts == 0) P = even;
+  }
   if (P == 0 || !parts_ok(ny, P, fp64))
     return fail(CF_ERR_UNSUPPORTED,
                 fp64 ? "ny needs P <= 64 partitions of M = ceil(ny/P) rows, M in {1,2,3,4,6,8,12,16}, "
@@ -1099,6 +1129,13 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
   if (e != hipSuccess) {
     delete pl;
     return dev_fail(e, "hipGetSymbolAddress (interface-row scratch)");
+  }
+  if (opt.n_parts == 0 && !tune) {
+    // the slab passes also take the slab counts that divide ny evenly, which
+    // the cheapest count for one device may not be a multiple of
+    const int even = even_parts(ny, fp64), rows = part_rows(ny, even);
+    const int elb = cf::ysolve_default_lb(even, rows, fp64);
+    if (even != P && cf::ysolve_lds_needed(even * rows, even, elb, fp64) <= (size_t)lds_max) pl->slab_P = even;
   }
   const size_t lds_need = cf::ysolve_lds_needed(P * pl->M, P, LB, opt.precision == CF_FP64);
   if (lds_need > (size_t)lds_max) {
@@ -1315,7 +1352,7 @@ cf_status cf_plan_query(const cf_plan* pl, cf_plan_info* info) {
   info->k2_threshold = pl->k2drop;
   info->workspace_bytes = pl->bytes;
   info->lines_per_block = pl->LB;
-  info->slab_iface_bytes = (size_t)pl->P * 8 * (size_t)pl->nkx * pl->nz * (pl->mixed() ? sizeof(float) : sizeof(double));
+  info->slab_iface_bytes = slab_bytes(pl, std::max(pl->P, pl->slab_P));
   info->drop_parts = pl->G;
   info->n_dropped_lines = pl->n_dropped;
   return CF_OK;
@@ -1372,8 +1409,7 @@ cf_status cf_solve_spectral_slabs(cf_plan* pl, int n_slabs, const void* fhat, vo
   CF_TRY(check_disjoint(phat, spec_bytes(pl), fhat, spec_bytes(pl), true, "phat must be fhat itself or not overlap it"));
   CF_TRY(check_ptr(iface, "iface"));
   if (pl->opt.flags & CF_PLAN_Y_DCT) return fail(CF_ERR_ARG, "the y-transform solve has no partitions");
-  if (n_slabs < 1 || pl->P % n_slabs != 0)
-    return fail(CF_ERR_ARG, "n_slabs must divide the plan's partition count " + std::to_string(pl->P));
+  if (slab_parts(pl, n_slabs) == 0) return slab_refuse(pl);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (pl->mixed())
     return slabs_t<float>(pl, n_slabs, static_cast<const cx<float>*>(fhat), static_cast<cx<float>*>(phat), iface, s);
@@ -1386,9 +1422,9 @@ cf_status cf_solve_spectral_slabs_noalloc(cf_plan* pl, int n_slabs, const void* 
   CF_TRY(check_ptr(phat, "phat"));
   CF_TRY(check_disjoint(phat, spec_bytes(pl), fhat, spec_bytes(pl), true, "phat must be fhat itself or not overlap it"));
   if (pl->opt.flags & CF_PLAN_Y_DCT) return fail(CF_ERR_ARG, "the y-transform solve has no partitions");
-  if (n_slabs < 1 || pl->P % n_slabs != 0)
-    return fail(CF_ERR_ARG, "n_slabs must divide the plan's partition count " + std::to_string(pl->P));
-  const size_t need = (size_t)pl->P * 8 * (size_t)pl->nkx * pl->nz * (pl->mixed() ? sizeof(float) : sizeof(double));
+  const int P = slab_parts(pl, n_slabs);
+  if (P == 0) return slab_refuse(pl);
+  const size_t need = slab_bytes(pl, P);
   if (need > kSlabScratchBytes)
     return fail(CF_ERR_ARG, "the plan's interface rows need " + std::to_string(need) + " bytes, more than the " +
                                 std::to_string(kSlabScratchBytes) + "-byte static scratch");

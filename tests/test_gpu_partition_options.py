@@ -1,0 +1,56 @@
+"""Slab counts and drop_parts given to a plan whose partition count is
+automatic: counts that divide the even partitioning of ny (the fewest partitions
+that divide it) are taken, whatever count is the cheapest on one device."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2104_08863_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def make(ny, **kw):
+    from paper_2104_08863_amd.api import Plan
+    nx, nz = 32, 24
+    yf = synth.tanh_faces(ny, 2.0)
+    return Plan(nx, ny, nz, 2 * np.pi, np.pi, yf, **kw), O.Box(nx, ny, nz, 2 * np.pi, np.pi, yf)
+
+
+def spectrum(pl, seed):
+    rng = np.random.default_rng(seed)
+    fh = rng.standard_normal(pl.spec_shape) + 1j * rng.standard_normal(pl.spec_shape)
+    fh[0, :, 0].imag = 0.0
+    return torch.tensor(fh, device="cuda")
+
+
+# (ny, partitions of the even count): every divisor of it is a slab count.  45 =
+# 15 x 3, 54 = 9 x 6, 56 = 7 x 8, 27 = 9 x 3; 97 rows pad: 49 x 2 pads one row
+@pytest.mark.parametrize("ny,even", [(45, 15), (54, 9), (56, 7), (27, 9), (97, 49)])
+def test_slab_counts_of_the_even_partitioning(ny, even):
+    pl, box = make(ny)
+    fh = spectrum(pl, ny)
+    want = O.solve_spectral(fh.cpu().permute(1, 2, 0), box).permute(2, 0, 1).numpy()
+    scale = np.abs(want).max(axis=1)
+    counts = [g for g in range(1, even + 1) if even % g == 0 or pl.info()["n_parts"] % g == 0]
+    for g in counts:
+        got = pl.solve_spectral_slabs(fh, g)
+        noalloc = torch.empty_like(fh)
+        pl.solve_spectral_slabs_noalloc(fh, g, noalloc)
+        assert torch.equal(got, noalloc), g
+        if pl.info()["n_parts"] % g == 0:
+            assert torch.equal(got, pl.solve_spectral(fh)), g
+        # per line, the bound of the one-pass solve
+        assert (np.abs(got.cpu().numpy() - want).max(axis=1) / scale).max() <= 1e-11, g
+
+
+@pytest.mark.parametrize("ny,drop_parts", [(27, 3), (54, 9), (45, 5)])
+def test_drop_parts_of_the_even_partitioning(ny, drop_parts):
+    pl, box = make(ny, drop_parts=drop_parts)
+    info = pl.info()
+    assert info["drop_parts"] == drop_parts and info["n_parts"] % drop_parts == 0
+    fh = spectrum(pl, ny)
+    want = O.solve_spectral(fh.cpu().permute(1, 2, 0), box).permute(2, 0, 1).numpy()
+    got = pl.solve_spectral(fh).cpu().numpy()
+    assert (np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)).max() <= 1e-11
