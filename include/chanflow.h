@@ -63,10 +63,10 @@ typedef struct {
                          divide ny the last partition is padded with decoupled rows */
   double drop_tol;    /* lines whose PDD corner terms are all <= drop_tol use the dropped
                          (2x2) reduced system; the others the exact one.  < 0 = default
-                         (1e-15 FP64, 1e-7 mixed).  At the default or below it the two
-                         systems agree to the round-off of the precision, and the solve
-                         takes the exact one, which is faster on one device, for every
-                         line */
+                         (1e-15 FP64, 1e-7 mixed).  The two systems agree to the round-off
+                         of the precision there, and with drop_parts = 0 a default plan
+                         takes the exact one for every line where that is the faster
+                         one: CF_MIXED, and CF_FP64 with spectra below 1 GiB */
   int fp64_kx;        /* CF_MIXED: lines with kx < fp64_kx and min(kz, nz-kz) < fp64_kz */
   int fp64_kz;        /*   are solved in FP64 (default 4, 4) */
   int refine_passes;  /* CF_MIXED: FP64 residual + correction solves (default 1; one pass
@@ -115,10 +115,10 @@ typedef struct {
                               n_parts * 8 * n_lines values of the plan's precision (of
                               the larger count where slabs may take another one) */
   int drop_parts;         /* G, the outer partitions of the dropped reduced system */
-  long long n_dropped_lines; /* lines whose block of lines_per_block consecutive lines lies
-                              wholly above k2_threshold: those the partitioned solve may drop
-                              the corner terms for, and does when drop_tol is above its
-                              default (the others take the exact reduced system) */
+  long long n_dropped_lines; /* lines the partitioned solve drops the corner terms for: those
+                              whose block of lines_per_block consecutive lines lies wholly
+                              above k2_threshold (the others take the exact reduced system);
+                              0 for a default plan that takes the exact one throughout */
 } cf_plan_info;
 
 /* Fill *opt with the defaults. */

@@ -110,9 +110,7 @@ struct cf_plan {
   // then the dropped one)
   std::vector<int> blocks_exact, blocks_drop;
   int* d_blocks = nullptr;
-  // drop_tol is at the round-off of the precision: the exact and the dropped
-  // reduced system then give the same solution, and every block takes the
-  // exact one, which is the faster kernel on one device
+  // No block drops (blocks_exact and blocks_drop stay empty): see takes_exact.
   bool exact_all = false;
   // partition counts and block shapes timed at creation (CF_PLAN_TUNE_PARTS)
   struct TuneRow {
@@ -403,6 +401,7 @@ void set_partitions(cf_plan* pl, int P, int LB) {
   pl->n_dropped = 0;
   pl->blocks_exact.clear();
   pl->blocks_drop.clear();
+  if (pl->exact_all) return;
   for (long b0 = 0; b0 < nl; b0 += LB) {
     const long b1 = std::min(nl, b0 + LB);
     bool all = true;
@@ -414,6 +413,25 @@ void set_partitions(cf_plan* pl, int P, int LB) {
       pl->blocks_exact.push_back(int(b0 / LB));
     }
   }
+}
+
+// Whether a plan takes the exact reduced system for every line although its
+// tolerance would let some drop: where the caller leaves drop_tol and drop_parts
+// to the plan.  At the default tolerance, the round-off of the precision, the two
+// systems give the same solution, so the faster kernel may serve.  Exact against
+// dropped, us per line solve:
+//   CF_MIXED   128x96x128 8.4 / 15.4, 512x192x512 84 / 109, 1024x384x1024 585 / 649,
+//              2048x512x1536 2556 / 2566, 2048x768x2048 5422 / 5686
+//   CF_FP64    128x64x128 8.0 / 13.8 (the dropped blocks are a launch of their
+//              own), 512x128x256 52.7 / 55.4, 1024x128x512 (513 MiB of spectrum)
+//              196 / 203, 1024x192x512 (770 MiB) 303 / 304
+//   CF_FP64 from 1 GiB: neither, within 4.5 % either way (512x512x512 401 / 396,
+//              1024x256x512 372 / 376, 1024x384x512 659 / 644, 1024x256x1024 744 /
+//              739, 2048x128x1024 662 / 692, 2048x384x1024 2635 / 2540,
+//              2048x512x1024 3277 / 3392): the lines above the threshold drop
+bool takes_exact(const cf_options& opt, size_t spectrum_bytes) {
+  if (opt.drop_tol >= 0 || opt.drop_parts > 0) return false;
+  return opt.precision == CF_MIXED || spectrum_bytes < (size_t(1) << 30);
 }
 
 // Copies the block lists of set_partitions to the device (synchronously).
@@ -1049,8 +1067,9 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
     if (opt.fp64_kx < 1 || opt.fp64_kz < 1) return fail(CF_ERR_ARG, "fp64_kx and fp64_kz must be >= 1");
     if (opt.refine_passes < 0 || opt.refine_passes > 8) return fail(CF_ERR_ARG, "refine_passes must be in [0, 8]");
   }
-  const double round_off = (opt.precision == CF_MIXED) ? 1e-7 : 1e-15;
-  if (opt.drop_tol < 0) opt.drop_tol = round_off;
+  const size_t spec = (size_t)(nx / 2 + 1) * ny * nz * (fp64 ? sizeof(cx<double>) : sizeof(cx<float>));
+  const bool exact_all = takes_exact(opt, spec);
+  if (opt.drop_tol < 0) opt.drop_tol = fp64 ? 1e-15 : 1e-7;
   if (opt.flags & CF_PLAN_Y_DCT) {
     if (opt.precision != CF_FP64) return fail(CF_ERR_UNSUPPORTED, "the y-transform solve is FP64 only");
     if (ny % 2 != 0 || !cf::ydct_len_compiled(ny))
@@ -1072,7 +1091,7 @@ cf_status cf_plan_create(cf_plan** out, int nx, int ny, int nz, double lx, doubl
   pl->dx = lx / nx;
   pl->dz = lz / nz;
   pl->opt = opt;
-  pl->exact_all = opt.drop_tol <= round_off;
+  pl->exact_all = exact_all;
   pl->P = P;
   pl->M = part_rows(ny, P);
   pl->yf.assign(y_faces, y_faces + ny + 1);
