@@ -90,10 +90,13 @@ typedef struct {
    relative), CF_FP64, and an even ny of the form 2^a or 3*2^a, at most 2048. */
 /* CF_PLAN_TUNE_PARTS: choose the partitioning by measurement (Section 2.2 leaves
    the count P and the placement to the solver): at creation the plan times the
-   partitioned solve for every admissible P (M = ceil(ny/P) in {1,2,3,4,6,8,12,16},
-   in CF_MIXED also 24 and 32, (P-1)*M < ny, P <= 64) and every block of lines_per_block = 4, 8, ..., 256 lines with
-   64 <= lines_per_block * P <= 512 that fits in LDS (five launches each, after
-   two warm-up launches, in place on zeros in the plan's workspace), keeps the
+   partitioned solve for every P <= 64 that divides ny into M rows (M one of
+   1,2,3,4,6,8,12,16, in CF_MIXED also 24 and 32; if none does, for every P with
+   M = ceil(ny/P) of these and (P-1)*M < ny) and for the automatic P, with every
+   block of lines_per_block = 4, 8, ..., 256 lines with 64 <= lines_per_block * P
+   <= 512 that fits in LDS and, on grids of at least 256 such blocks, the default
+   block of P (five launches each, after two warm-up launches, in place on zeros
+   in the plan's workspace), keeps the
    fastest and sets the drop threshold for its P (each candidate's accuracy
    follows drop_tol, so the choice affects speed, not the error bound).  Needs
    n_parts = 0, lines_per_block = 0 and the partitioned solve (no CF_PLAN_Y_DCT);

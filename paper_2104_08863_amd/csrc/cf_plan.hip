@@ -936,9 +936,11 @@ void special_factors(const cf_plan* pl, int line, double* alpha, double* rden, d
 // Partition count and block shape by measurement (the count and placement
 // question of Section 2.2, answered on the device): every P with ny = P*M for
 // a compiled M, P <= 64 (if there is none, every padded partitioning that
-// parts_ok admits), and every block of LB lines with 64 <= LB*P <= 512
-// threads that fits in LDS, is timed over five launches of the partitioned
-// solve (in place, on zeros in the plan's spectral workspace, on the plan's
+// parts_ok admits), and the automatic P; with each, every block of LB = 4, 8,
+// ..., 256 lines with 64 <= LB*P <= 512 threads that fits in LDS, and the
+// default block of that P where such blocks fill the chip (fewer do not tell
+// block shapes apart), so that an untuned plan's pair is among them.  Each is
+// timed over five launches of the partitioned solve (in place, on zeros in the plan's spectral workspace, on the plan's
 // capture stream, after two warm-up launches); the fastest is kept and the drop
 // threshold follows its P.
 cf_status tune_partitions(cf_plan* pl, size_t lds_max) {
@@ -962,11 +964,16 @@ cf_status tune_partitions(cf_plan* pl, size_t lds_max) {
   // the partition counts that divide ny, or the padded ones when none does
   bool any_exact = false;
   for (int P = 1; P <= 64; ++P) any_exact = any_exact || (pl->ny % P == 0 && parts_ok(pl->ny, P, fp64));
+  const int P0 = auto_parts(pl->ny, fp64);
   for (int P = 1; P <= 64; ++P) {
-    if (!parts_ok(pl->ny, P, fp64) || (any_exact && pl->ny % P != 0)) continue;
-    for (int LB = 4; LB <= 256; LB *= 2) {
-      if (LB * P < 64 || LB * P > 512 || cf::ysolve_lds_needed(P * part_rows(pl->ny, P), P, LB, fp64) > lds_max)
-        continue;
+    if (!parts_ok(pl->ny, P, fp64) || (any_exact && pl->ny % P != 0 && P != P0)) continue;
+    std::vector<int> lbs;
+    for (int LB = 4; LB <= 256; LB *= 2)
+      if (LB * P >= 64) lbs.push_back(LB);
+    const int lb0 = cf::ysolve_default_lb(P, part_rows(pl->ny, P), fp64);
+    if ((lb0 & (lb0 - 1)) != 0 && (long)pl->nkx * pl->nz >= (long)lb0 * cf::kCus) lbs.push_back(lb0);
+    for (const int LB : lbs) {
+      if (LB * P > 512 || cf::ysolve_lds_needed(P * part_rows(pl->ny, P), P, LB, fp64) > lds_max) continue;
       set_partitions(pl, P, LB);
       if (upload_blocks(pl) != CF_OK) return done(CF_ERR_DEVICE);
       for (int r = 0; r < kWarm + kRuns && e == hipSuccess; ++r) {

@@ -1,6 +1,7 @@
 """Slab counts and drop_parts given to a plan whose partition count is
 automatic: counts that divide the even partitioning of ny (the fewest partitions
-that divide it) are taken, whatever count is the cheapest on one device."""
+that divide it) are taken, whatever count is the cheapest on one device.  And a
+plan tuned by measurement times what an untuned one would take."""
 import numpy as np
 import pytest
 import torch
@@ -11,9 +12,8 @@ from paper_2104_08863_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-def make(ny, **kw):
+def make(ny, nx=32, nz=24, **kw):
     from paper_2104_08863_amd.api import Plan
-    nx, nz = 32, 24
     yf = synth.tanh_faces(ny, 2.0)
     return Plan(nx, ny, nz, 2 * np.pi, np.pi, yf, **kw), O.Box(nx, ny, nz, 2 * np.pi, np.pi, yf)
 
@@ -54,3 +54,23 @@ def test_drop_parts_of_the_even_partitioning(ny, drop_parts):
     want = O.solve_spectral(fh.cpu().permute(1, 2, 0), box).permute(2, 0, 1).numpy()
     got = pl.solve_spectral(fh).cpu().numpy()
     assert (np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)).max() <= 1e-11
+
+
+# 144 = 9 x 16 with blocks of 24 lines; 102 rows as 9 x 12, padded although 17 x 6
+# divides; 65 * 96 lines make 260 blocks of 24
+@pytest.mark.parametrize("ny", [144, 102])
+def test_tuning_times_the_untuned_pair(ny):
+    auto, _ = make(ny, 128, 96)
+    pair = auto.info()["n_parts"], auto.info()["lines_per_block"]
+    assert pair == (9, 24)
+    pl, box = make(ny, 128, 96, tune_parts=True)
+    rows = pl.partition_timings()
+    assert len({r[:2] for r in rows}) == len(rows) and pair in {r[:2] for r in rows}
+    best = min(rows, key=lambda r: r[2])
+    assert (pl.info()["n_parts"], pl.info()["lines_per_block"]) == best[:2]
+    f = torch.tensor(synth.uniform_rhs(128, ny, 96, seed=ny), device="cuda")
+    p = pl.poisson_solve(f)
+    same, _ = make(ny, 128, 96, n_parts=best[0], lines_per_block=best[1])
+    assert torch.equal(p, same.poisson_solve(f))
+    ref = O.poisson(f.cpu(), box)
+    assert float((p.cpu() - ref).norm() / ref.norm()) <= 1e-12
