@@ -239,8 +239,11 @@ cf_status cf_plane_stats(cf_plan* plan, const void* u, const void* v, const void
  * use_graph != 0 replays the steps from HIP graphs on a plan-owned stream
  * (ordered after earlier work on `stream`, and later work on `stream` after
  * it): one recorded step per parity, with and without the statistics pass, and
- * two consecutive steps where neither takes statistics, kept in the plan (up to 8, least recently used dropped) and reused by later calls
- * with the same arrays and parameters, which removes the per-launch host cost.
+ * two consecutive steps where neither takes statistics, kept in the plan (up to
+ * 10, least recently used dropped) and reused by later calls with the same arrays
+ * and parameters.  That frees the host of the per-launch cost; on the device a
+ * graph starts later than a launch in a stream, so that a loop whose host keeps
+ * ahead is faster without graphs (64^3 FP64 by 14 %, 256x128x256 by 1 %).
  * Results are identical in both modes.
  * The plan must have been created with CF_PLAN_STEP.
  */

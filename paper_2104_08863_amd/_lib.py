@@ -76,6 +76,8 @@ HOST_SIGNATURES = {
     "cfh_pdd_line": (_I, [_I, _I, _P, _P, _D, _I, _I, _P, _P]),
     "cfh_pdd_line_grouped": (_I, [_I, _I, _I, _P, _P, _D, _I, _P, _P]),
     "cfh_xcd_slab_block": (_I, [_I, _I]),
+    "cfh_loop_graphs": (_I, [_I, _I]),
+    "cfh_max_graphs": (_I, []),
 }
 
 _lib = None

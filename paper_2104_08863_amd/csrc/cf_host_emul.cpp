@@ -10,6 +10,7 @@
 
 #include "cf_fft.h"
 #include "cf_pdd.h"
+#include "cf_rules.h"
 
 using cf::cx;
 using cf::mk;
@@ -298,5 +299,20 @@ int cfh_pdd_line_grouped(int ny, int P, int G, const double* a, const double* c,
 // on a contiguous run of every group): the index map of the row-block and
 // stencil-tile launches.
 int cfh_xcd_slab_block(int b, int n) { return cf::xcd_slab_block(b, n); }
+
+// Graphs a time loop of nsteps steps replays (distinct by parity and kind), and
+// how many a plan keeps.
+int cfh_loop_graphs(int nsteps, int stats_every) {
+  bool used[2][cf::kLoopGraphs] = {};
+  int n = 0;
+  for (int k = 0; k < nsteps;) {
+    const cf::LoopGraph g = cf::loop_graph(k, nsteps, stats_every);
+    n += !used[k & 1][g];
+    used[k & 1][g] = true;
+    k += g == cf::kTwoSteps ? 2 : 1;
+  }
+  return n;
+}
+int cfh_max_graphs() { return (int)cf::kMaxGraphs; }
 
 }

@@ -21,6 +21,7 @@
 #include "cf_fft.h"
 #include "cf_internal.h"
 #include "cf_pdd.h"
+#include "cf_rules.h"
 #include "cf_adjoint_kernels.h"
 #include "cf_step_kernels.h"
 
@@ -1639,7 +1640,7 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(CF_ERR_ARG, "dt must be finite and > 0");
   if (!(nu >= 0.0) || !std::isfinite(nu) || !std::isfinite(fx)) return fail(CF_ERR_ARG, "nu >= 0 and fx must be finite");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  auto acc_at = [&](int step) -> double* { return (stats_every > 0 && (step + 1) % stats_every == 0) ? stats_acc : nullptr; };
+  auto acc_at = [&](int k) -> double* { return cf::loop_stats_at(k, stats_every) ? stats_acc : nullptr; };
   if (!use_graph) {
     for (int k = 0; k < nsteps; ++k) CF_TRY(loop_step(pl, (k & 1) ? B : A, (k & 1) ? A : B, p, dt, nu, fx, acc_at(k), s));
     return CF_OK;
@@ -1653,9 +1654,7 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
   // most kMaxGraphs entries; the least recently used one is dropped after the
   // capture stream has drained).  Per-launch event timing
   // is not recorded into graphs.
-  constexpr size_t kMaxGraphs = 8;
-  enum { kOne, kStats, kTwo, kKinds };
-  auto kind_at = [&](int k) { return acc_at(k) ? kStats : k + 1 < nsteps && !acc_at(k + 1) ? kTwo : kOne; };
+  auto kind_at = [&](int k) { return cf::loop_graph(k, nsteps, stats_every); };
   auto find = [&](void* const* a, void* const* b, double* acc, int steps) -> hipGraphExec_t {
     for (auto& g : pl->graphs)
       if (g.a[0] == a[0] && g.a[1] == a[1] && g.a[2] == a[2] && g.b[0] == b[0] && g.b[1] == b[1] &&
@@ -1666,17 +1665,17 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
       }
     return nullptr;
   };
-  hipGraphExec_t ex[2][kKinds] = {};
+  hipGraphExec_t ex[2][cf::kLoopGraphs] = {};
   for (int k = 0, steps; k < nsteps; k += steps) {
     const int par = k & 1, kind = kind_at(k);
-    steps = kind == kTwo ? 2 : 1;
+    steps = kind == cf::kTwoSteps ? 2 : 1;
     if (ex[par][kind]) continue;
     void* const* a = par ? B : A;
     void* const* b = par ? A : B;
-    double* acc = kind == kStats ? stats_acc : nullptr;
+    double* acc = kind == cf::kStatsStep ? stats_acc : nullptr;
     ex[par][kind] = find(a, b, acc, steps);
     if (ex[par][kind]) continue;
-    if (pl->graphs.size() >= kMaxGraphs) {
+    if (pl->graphs.size() >= cf::kMaxGraphs) {
       CF_HIP(hipStreamSynchronize(pl->gstream), "hipStreamSynchronize");
       size_t old = 0;
       for (size_t q = 1; q < pl->graphs.size(); ++q)
@@ -1713,7 +1712,7 @@ cf_status cf_run_steps(cf_plan* pl, void* u, void* v, void* w, void* u2, void* v
   }
   hipError_t e = hipEventRecord(pl->ev_gin, s);
   if (e == hipSuccess) e = hipStreamWaitEvent(pl->gstream, pl->ev_gin, 0);
-  for (int k = 0; k < nsteps && e == hipSuccess; k += kind_at(k) == kTwo ? 2 : 1)
+  for (int k = 0; k < nsteps && e == hipSuccess; k += kind_at(k) == cf::kTwoSteps ? 2 : 1)
     e = hipGraphLaunch(ex[k & 1][kind_at(k)], pl->gstream);
   if (e == hipSuccess) e = hipEventRecord(pl->ev_gout, pl->gstream);
   if (e == hipSuccess) e = hipStreamWaitEvent(s, pl->ev_gout, 0);
