@@ -44,9 +44,11 @@ __device__ __forceinline__ int mk_pos(int j) {
 // Lines (kx, kz0 .. kz0+LB-1) of layout B (nkx, ny, nz) per block; in place
 // allowed (a block reads its lines completely before writing them).
 // Only the moves of the block's rows into and out of LDS cross lines; between
-// them a line's threads order their own accesses (line_sync).  NT: rows read and
-// written once, streamed for large spectra.
-template <typename T, int N, bool NT>
+// them a line's threads order their own accesses (line_sync).  Rows are cached
+// loads and stores at every size: streamed, the whole solve is 0.1-0.8 % slower
+// (us cached / streamed with spectra of 0.5 GiB 1022 / 1037, 1.0 GiB 2081 / 2093,
+// 1.5 GiB 3529 / 3536, 4 GiB 8930 / 8959, 8 GiB 18644 / 18746).
+template <typename T, int N>
 __global__ void __launch_bounds__((YdctCfg<T, N>::THREADS))
 k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>* __restrict__ wq,
        const T* __restrict__ lam, const T* __restrict__ kx2, const T* __restrict__ kz2, int nz) {
@@ -67,7 +69,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
 #pragma unroll
     for (int r = 0; r < PT; ++r) {
       const int idx = threadIdx.x + r * TH, q = idx % LB, j = idx / LB;
-      ld[r] = (kz0 + q < nz) ? ld_once<NT>(&fin[base + (long)j * nz + q]) : mk(T(0), T(0));
+      ld[r] = (kz0 + q < nz) ? fin[base + (long)j * nz + q] : mk(T(0), T(0));
     }
 #pragma unroll
     for (int r = 0; r < PT; ++r) {
@@ -151,7 +153,7 @@ k_ydct(const cx<T>* fin, cx<T>* pout, const cx<T>* __restrict__ tw, const cx<T>*
 #pragma unroll 4
   for (int idx = threadIdx.x; idx < N * LB; idx += TH) {
     const int q = idx % LB, j = idx / LB;
-    if (kz0 + q < nz) st_once<NT>(lds[q * S + lpad(j)], &pout[base + (long)j * nz + q]);
+    if (kz0 + q < nz) pout[base + (long)j * nz + q] = lds[q * S + lpad(j)];
   }
 }
 
@@ -161,10 +163,7 @@ static hipError_t ydct_n(const cx<T>* fin, cx<T>* pout, const cx<T>* tw, const c
   using C = YdctCfg<T, N>;
   const long blocks = (long)nkx * ((nz + C::LB - 1) / C::LB);
   if (blocks <= 0) return hipSuccess;
-  if ((long)nkx * nz * N * (long)sizeof(cx<T>) >= kStreamSolve)
-    hipLaunchKernelGGL((k_ydct<T, N, true>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
-  else
-    hipLaunchKernelGGL((k_ydct<T, N, false>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
+  hipLaunchKernelGGL((k_ydct<T, N>), dim3(blocks), dim3(C::THREADS), 0, s, fin, pout, tw, wq, lam, kx2, kz2, nz);
   return hipGetLastError();
 }
 
