@@ -119,15 +119,26 @@ __device__ __forceinline__ void line_sync() {
 // Smaller arrays stay cached for the next kernel (streamed, the 64^3 time loop
 // was 2-4 % slower).
 constexpr long kStreamBytes = 32L << 20;
-// The spectrum sizes from which the z transforms and the wall-normal solve
-// stream.  What they store without it is partly still in the 256 MB cache behind
-// the L2s when the next kernel of the solve reads it: FP64 Poisson solve, both
-// cached against both streamed, 64 MiB 148 -> 131 us, 109 MiB 232 -> 212, 128 MiB
-// 263 -> 246.  Beyond that two cached neighbours push each other out (193 MiB, the
-// solve cached and the z transforms streamed 949 us, both cached 1031, both
-// streamed 998), and at 1.5 GiB the solve gains by streaming too (1 %).
+// The spectrum sizes from which the z transforms and the one-pass wall-normal
+// solve stream.  What they store without it is partly still in the 256 MB cache
+// behind the L2s when the next kernel of the solve reads it: FP64 Poisson solve,
+// both cached against both streamed, 64 MiB 148 -> 131 us, 109 MiB 232 -> 212, 128
+// MiB 263 -> 246.  Beyond that two cached neighbours push each other out (193 MiB,
+// the solve cached and the z transforms streamed 949 us, both cached 1031, both
+// streamed 998).
 constexpr long kStreamZ = 160L << 20;
-constexpr long kStreamSolve = 1280L << 20;
+// The wall-normal solve beside streamed z transforms, whole Poisson solve in us,
+// its arrays cached / streamed:
+//   FP64  257 MiB 473 / 490, 514 MiB 953 / 964, 770 MiB 1484 / 1492, 1.0 GiB 1943 /
+//         1947, 1.25 GiB 2603 / 2624, 1.5 GiB 3058 / 3080, 2 GiB 4016 / 4025 (within
+//         a step 11000 / 10984), 3 GiB 6369 / 6334, 4 GiB 8108 / 8078, 8 GiB 17031 /
+//         16927
+//   FP32  256 MiB 1308 / 1363, 513 MiB 2674 / 2703, 770 MiB 4058 / 4070, 1.0 GiB
+//         5515 / 5507, 1.25 GiB 7096 / 7035, 1.5 GiB 8377 / 8272, 4 GiB 23105 / 22897
+// The kernel alone gains earlier (FP64 1.0 GiB, in a step: 399 / 387 us) what the
+// kernels next to it lose (the step: 5471 / 5467).
+template <typename T>
+constexpr long kStreamSolve = (sizeof(T) == 8 ? 2048L : 1024L) << 20;
 
 // Compute units of the chip (8 XCDs of 32).
 constexpr int kCus = 256;

@@ -60,7 +60,7 @@ static hipError_t ysolve_go(long blocks, const int* blist, const YArgs& ya, int 
   if constexpr (MODE == kWhole) {
     // the slab passes read their right-hand side twice: only the one-pass
     // solve streams it
-    if ((long)ya.nlines * ya.ny * (long)sizeof(cx<T>) >= kStreamSolve) {
+    if ((long)ya.nlines * ya.ny * (long)sizeof(cx<T>) >= kStreamSolve<T>) {
       hipLaunchKernelGGL((k_ysolve<T, M, MODE, DROP, true>), dim3(blocks), dim3(threads), lds, s, fin, pout, a, c,
                          kx2, kz2, blist, ya, sp);
       return hipGetLastError();
