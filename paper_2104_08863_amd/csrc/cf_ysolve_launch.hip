@@ -30,10 +30,17 @@ bool ysolve_m_compiled(int m, bool fp64) {
 //     multiples of 8 (9 x 16 rows: 59 us at 24 lines, 65 at 28, 69 at 16), or 12
 //     lines where 16 do not fit (19 x 16 rows: 143 us at 12 lines, 165 at 8; at
 //     13 lines, which 256 threads would take, 255).
-//   FP32: 16 lines (25 x 12 rows: 104 us, 204 at 10; 13 x 24 rows: 72 us, 167 at
-//     19), 32 where at most 8 partitions leave the block small, and for 16
-//     partitions of 24 rows (1024x384x1024: 574 us, 659 at 16).
-// At least one wave and, above 32 partitions, what 512 threads hold.
+//   FP32: 16 lines (25 x 12 rows: 104 us, 204 at 10; 13 x 24 rows: 167 us at 19),
+//     32 where at most 8 partitions leave the block small, 8 above 32 partitions
+//     (at most 512 threads), and 32 for 13 to 16 partitions of 24 rows, whose
+//     instance is held to 128 VGPRs so that two blocks of 512 threads share a CU.
+//     us at 16 / 32 lines on 512 x 24P x 256, 1024 x 24P x 512 and 1024 x 24P x
+//     1024: P = 11 64 / 70, 243 / 250, 476 / 478; 12 73 / 77, 268 / 263, 527 / 505;
+//     13 79 / 76, 285 / 273, 560 / 529; 14 84 / 84, 308 / 291, 561 / 537; 15 89 / 87,
+//     327 / 297, 606 / 543; 16 95 / 91, 356 / 317, 648 / 577.  Other rows are slower
+//     at 32 lines from P = 9 on (512 x 16P x 256: P = 9 33 / 41, 16 52 / 57; of 32
+//     rows: 83 / 110, 123 / 151).
+// At least one wave.
 int ysolve_default_lb(int P, int M, bool fp64) {
   int lb;
   if (fp64) {
@@ -41,9 +48,8 @@ int ysolve_default_lb(int P, int M, bool fp64) {
     lb = lb >= 16 ? lb & ~7 : (lb >= 12 ? 12 : 8);
     if (lb > 48) lb = 48;
   } else {
-    lb = P <= 8 || (P == 16 && M == 24) ? 32 : 16;
+    lb = P <= 8 || (M == 24 && P >= 13 && P <= 16) ? 32 : P <= 32 ? 16 : 8;
   }
-  if (lb * P > 512) lb = P <= 64 ? 8 : 512 / P;
   if (lb * P < 64) lb = (64 + P - 1) / P;
   return lb;
 }

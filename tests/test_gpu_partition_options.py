@@ -1,7 +1,8 @@
 """Slab counts and drop_parts given to a plan whose partition count is
 automatic: counts that divide the even partitioning of ny (the fewest partitions
 that divide it) are taken, whatever count is the cheapest on one device.  And a
-plan tuned by measurement times what an untuned one would take."""
+plan tuned by measurement times what an untuned one would take, and the default
+blocks of the FP32 partitions of 24 rows."""
 import numpy as np
 import pytest
 import torch
@@ -74,3 +75,14 @@ def test_tuning_times_the_untuned_pair(ny):
     assert torch.equal(p, same.poisson_solve(f))
     ref = O.poisson(f.cpu(), box)
     assert float((p.cpu() - ref).norm() / ref.norm()) <= 1e-12
+
+
+# FP32 partitions of 24 rows: 32 lines per block from 13 to 16 of them, 16 either side
+@pytest.mark.parametrize("parts,lb", [(11, 16), (13, 32), (14, 32), (15, 32), (16, 32), (32, 16)])
+def test_block_of_the_24_row_partitions(parts, lb):
+    ny = 24 * parts
+    pl, _ = make(ny, precision="mixed")
+    assert (pl.info()["n_parts"], pl.info()["rows_per_part"], pl.info()["lines_per_block"]) == (parts, 24, lb)
+    other, _ = make(ny, precision="mixed", n_parts=parts, lines_per_block=8)
+    fh = spectrum(pl, ny).to(torch.complex64)
+    assert torch.equal(pl.solve_spectral(fh), other.solve_spectral(fh))
