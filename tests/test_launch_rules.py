@@ -23,3 +23,22 @@ def test_alternating_loops_keep_their_graphs(H):
             mine, single = H.cfh_loop_graphs(nsteps, every), single_step_graphs(nsteps, every)
             assert mine <= 5
             assert (8 // single) * mine <= H.cfh_max_graphs(), (nsteps, every)
+
+
+@pytest.mark.parametrize("most,extra", [(32, 2), (128, 4)])
+def test_chunk_lengths(H, most, extra):
+    """Chunks are within their limits and within 4 % of the least rounds of blocks
+    times planes; a grid of few columns fills the chip, one of many takes the
+    longest chunks it can."""
+    for ny in (1, 2, 3, 31, 32, 33, 62, 97, 128, 130, 250, 256, 1024):
+        for cols in (1, 4, 64, 300, 768, 1536, 65536):
+            for slots in (256, 512, 768):
+                cost = lambda cy: -(-(cols * -(-ny // cy)) // slots) * (cy + extra)  # noqa: E731
+                cy = H.cfh_chunk_planes(cols, ny, slots, most, extra)
+                top = min(most, ny)
+                assert 1 <= cy <= top
+                least = min(cost(c) for c in range(1, top + 1))
+                assert 100 * cost(cy) <= 104 * least
+                assert all(100 * cost(c) > 104 * least for c in range(cy + 1, top + 1))
+    assert H.cfh_chunk_planes(4, 64, 256, 128, 4) == 1       # four columns: one plane per block
+    assert H.cfh_chunk_planes(65536, 64, 768, 32, 2) == 32
