@@ -50,10 +50,11 @@ constexpr RadixPlan make_radix_plan(int n) {
   return p;
 }
 
-// FP64 radices with fewer elements per thread where that costs no pass: 12 for
-// N = 3 * 2^a up to 768 (4s and a last 6 or 12; 24 elements are 96 registers and
-// leave half-filled waves in the x transforms), 4 and 8 for N = 16, 32 and 64
-// (the chain of one thread is most of a short transform's time).
+// FP64 radices with fewer elements per thread: 12 for N = 3 * 2^a up to 768 (4s
+// and a last 6 or 12, in no more passes; 24 elements are 96 registers and leave
+// half-filled waves in the x transforms), 4 and 8 for N = 16, 32 and 64 (the chain
+// of one thread is most of a short transform's time; N = 16 takes two passes for
+// one).
 constexpr RadixPlan make_radix_plan_fp64(int n) {
   RadixPlan p{0, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, 1};
   if (n % 3 == 0 && n >= 24 && n <= 768) {

@@ -292,6 +292,11 @@ CF_HD float* rows32(double* row, int k, int nx) {
 // Tp = float: every row of the FP64 array p holds that row's nx values as
 // FP32 in one half of its bytes (the FP32 solve's output before the first
 // correction is added; see rows32), read exactly as FP64.
+// Two pairs in flight spill in the longest FP32 rows (27 registers at 2048 points:
+// the mixed 2048x512x1536 solve moves 184.8 GB, with one pair 166) and are still
+// the faster: that solve's two forward transforms 11.58 ms against 11.62, with a
+// divergence as inner source 427 us against 432 on 512x192x512 and 3.62 ms against
+// 3.66 on 1024x384x1024.
 template <typename T, typename In, typename Tp = double>
 struct SrcResidual {
   static constexpr bool kPSum = true;
