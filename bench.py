@@ -47,8 +47,8 @@ MODEL_BYTES_PER_POINT = {
 # profiles/ are keyed to a hash of these files and the compile flags, so a
 # kernel changed since its counters were taken reports no traffic).
 KERNEL_SOURCES = {
-    "rk2_fused": ["cf_common.h", "cf_step_kernels.h", "cf_rk_fused.h", "cf_step_launch.hip"],
-    "correct": ["cf_common.h", "cf_step_kernels.h", "cf_rk_fused.h", "cf_step_launch.hip"],
+    "rk2_fused": ["cf_common.h", "cf_rules.h", "cf_step_kernels.h", "cf_rk_fused.h", "cf_step_launch.hip"],
+    "correct": ["cf_common.h", "cf_rules.h", "cf_step_kernels.h", "cf_rk_fused.h", "cf_step_launch.hip"],
     "r2c_x": ["cf_common.h", "cf_fft.h", "cf_fft_kernels.h", "cf_fft_launch.hip"],
     "c2r_x": ["cf_common.h", "cf_fft.h", "cf_fft_kernels.h", "cf_fft_launch.hip"],
     "fft_z_fwd": ["cf_common.h", "cf_fft.h", "cf_fft_kernels.h", "cf_fft_launch.hip"],
@@ -56,7 +56,7 @@ KERNEL_SOURCES = {
     "ysolve": ["cf_common.h", "cf_pdd.h", "cf_ysolve_kernels.h", "cf_ysolve_launch.hip"],
     # whole paths: every kernel source they launch and the plan that sequences them
     "step_fp64": ["cf_common.h", "cf_fft.h", "cf_fft_kernels.h", "cf_fft_launch.hip", "cf_pdd.h",
-                  "cf_ysolve_kernels.h", "cf_ysolve_launch.hip", "cf_step_kernels.h", "cf_rk_fused.h",
+                  "cf_ysolve_kernels.h", "cf_ysolve_launch.hip", "cf_rules.h", "cf_step_kernels.h", "cf_rk_fused.h",
                   "cf_step_launch.hip", "cf_plan.hip"],
     "poisson_mixed": ["cf_common.h", "cf_fft.h", "cf_fft_kernels.h", "cf_fft_launch.hip", "cf_pdd.h",
                       "cf_ysolve_kernels.h", "cf_ysolve_launch.hip", "cf_plan.hip"],

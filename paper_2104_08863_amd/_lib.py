@@ -78,6 +78,7 @@ HOST_SIGNATURES = {
     "cfh_xcd_slab_block": (_I, [_I, _I]),
     "cfh_loop_graphs": (_I, [_I, _I]),
     "cfh_max_graphs": (_I, []),
+    "cfh_correction_threads": (_I, [_I]),
     "cfh_chunk_planes": (_I, [_I, _I, _I, _I, _I]),
 }
 

@@ -55,7 +55,7 @@ template <typename T>
 hipError_t launch_correct_w(const T* gu, const T* gv, const T* gw, T* ou, T* ov, T* ow, const double* phi,
                             const AdjGeo<T>& g, hipStream_t st) {
   const long n = (long)g.g.nx * g.g.ny * g.g.nz;
-  const int th = 256;
+  const int th = correction_threads(g.g.nx);
   const dim3 blocks((g.g.nx / 2 * g.g.nz + th - 1) / th, g.g.ny);
   if (n * (long)sizeof(T) >= kStreamBytes)
     hipLaunchKernelGGL((k_correct_w<T, true>), blocks, dim3(th), 0, st, gu, gv, gw, ou, ov, ow, phi, g);

@@ -315,6 +315,9 @@ int cfh_loop_graphs(int nsteps, int stats_every) {
 }
 int cfh_max_graphs() { return (int)cf::kMaxGraphs; }
 
+// Threads per block of the pressure corrections.
+int cfh_correction_threads(int nx) { return cf::correction_threads(nx); }
+
 // Planes per y-chunk of a marching kernel.
 int cfh_chunk_planes(int cols, int ny, int slots, int max_planes, int extra) {
   return cf::chunk_planes(cols, ny, slots, max_planes, extra);

@@ -170,7 +170,7 @@ struct cf_plan {
   cf::Geo<float> g32{};
 
   bool mixed() const { return opt.precision == CF_MIXED; }
-  // side stream for the whole-line solves, which overlap the PDD kernel
+  // side stream for the whole-line solves beside the slab finishing passes
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // stream on which step sequences are recorded into HIP graphs and replayed
@@ -419,17 +419,18 @@ void set_partitions(cf_plan* pl, int P, int LB) {
 // Whether a plan takes the exact reduced system for every line although its
 // tolerance would let some drop: where the caller leaves drop_tol and drop_parts
 // to the plan.  At the default tolerance, the round-off of the precision, the two
-// systems give the same solution, so the faster kernel may serve.  Exact against
-// dropped, us per line solve:
-//   CF_MIXED   128x96x128 8.4 / 15.4, 512x192x512 84 / 109, 1024x384x1024 585 / 649,
-//              2048x512x1536 2556 / 2566, 2048x768x2048 5422 / 5686
-//   CF_FP64    128x64x128 8.0 / 13.8 (the dropped blocks are a launch of their
-//              own), 512x128x256 52.7 / 55.4, 1024x128x512 (513 MiB of spectrum)
-//              196 / 203, 1024x192x512 (770 MiB) 303 / 304
-//   CF_FP64 from 1 GiB: neither, within 4.5 % either way (512x512x512 401 / 396,
-//              1024x256x512 372 / 376, 1024x384x512 659 / 644, 1024x256x1024 744 /
-//              739, 2048x128x1024 662 / 692, 2048x384x1024 2635 / 2540,
-//              2048x512x1024 3277 / 3392): the lines above the threshold drop
+// systems give the same solution, so the faster kernel may serve.  us exact /
+// dropped of the line solve, and of the whole Poisson solve:
+//   CF_MIXED   128x96x128 8.5 / 15.2, 78 / 97 (the dropped blocks are a launch of
+//              their own); 512x192x512 84 / 109, 947 / 1007; 1024x384x1024 589 / 670,
+//              8267 / 8474; 2048x512x1536 2777 / 2761, 34273 / 34511
+//   CF_FP64    128x64x128 7.9 / 13.4, 40 / 46; 512x128x256 (128 MiB of spectrum) 52.5 /
+//              55.1, 247 / 250; 1024x128x512 (513 MiB) 195 / 202, 970 / 967;
+//              1024x192x512 (770 MiB) 299 / 300, 1485 / 1488
+//   CF_FP64 from 1 GiB: neither; whole solves 1024x256x512 1962 / 1968, 512x512x512
+//              1966 / 1969, 1024x384x512 3092 / 3083, 1024x512x512 4039 / 4041,
+//              2048x128x1024 4045 / 4087, 2048x256x1024 8311 / 8260, 2048x384x1024
+//              13083 / 12991: the lines above the threshold drop
 bool takes_exact(const cf_options& opt, size_t spectrum_bytes) {
   if (opt.drop_tol >= 0 || opt.drop_parts > 0) return false;
   return opt.precision == CF_MIXED || spectrum_bytes < (size_t(1) << 30);

@@ -25,6 +25,18 @@ inline int chunk_planes(long cols, int ny, long slots, int max_planes, int extra
   return 1;
 }
 
+// Threads per block (a pair of points each) of the pressure corrections.  Blocks
+// are dealt to the 8 XCDs in turn, so where a row takes a multiple of 8 blocks the
+// block with the z- or y-neighbours of a block's pressure is on the same XCD and
+// finds them in its L2: rows of a multiple of 1024 points take 8 blocks of 64 to 256
+// threads.  us of the two corrections of a step and its adjoint, 256 threads / this
+// rule: 2048x256x1024 FP32 3477, 3504 / 3022, 3122 (one point per thread of 256 had
+// 8 blocks too: 3376, 3128), 2048x768x2048 FP32 20493, 21001 / 19021, 19195,
+// 2048x128x1024 FP64 2668, 2670 / 2450, 2562, 1024x256x512 FP64 1283, 1338 / 1228,
+// 1259, FP32 781, 785 / 781, 779, 3072x64x512 FP64 995, 1028 / 997, 1012.  Blocks of
+// 64 threads on shorter rows are slower (512x192x512 FP32 308, 303 / 319, 316).
+inline int correction_threads(int nx) { return nx % 1024 == 0 && nx <= 4096 ? nx / 16 : 256; }
+
 // Graphs a time loop replays: one step, one step with statistics, or two steps
 // without.
 enum LoopGraph { kOneStep, kStatsStep, kTwoSteps, kLoopGraphs };

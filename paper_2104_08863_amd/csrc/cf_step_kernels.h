@@ -300,7 +300,7 @@ __device__ __forceinline__ void correct_pair(T* u, T* v, T* w, const double* __r
 // take one 32-bit division.  Against one point per thread of the whole grid:
 // FP64 1024x256x512 1.274 -> 1.271 ms (5.9 TB/s), 256x128x256 81 -> 74 us, FP32
 // 512x192x512 338 -> 306 us (5.3 TB/s); of the scalar form with the plane's grid
-// the last took 333.
+// the last took 333.  Blocks of correction_threads.
 template <typename T, bool NT>
 __global__ void __launch_bounds__(256)
 k_correct(T* u, T* v, T* w, const double* __restrict__ p, Geo<T> g, T dt) {

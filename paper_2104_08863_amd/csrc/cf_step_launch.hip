@@ -70,7 +70,7 @@ hipError_t launch_rk2_fused(const T* u, const T* v, const T* w, T* uo, T* vo, T*
 template <typename T>
 hipError_t launch_correct(T* u, T* v, T* w, const double* p, const Geo<T>& g, T dt, hipStream_t s) {
   const long n = (long)g.nx * g.ny * g.nz;
-  const int th = 256;
+  const int th = correction_threads(g.nx);
   const dim3 blocks((g.nx / 2 * g.nz + th - 1) / th, g.ny);
   if (n * (long)sizeof(T) >= kStreamBytes)
     hipLaunchKernelGGL((k_correct<T, true>), blocks, dim3(th), 0, s, u, v, w, p, g, dt);

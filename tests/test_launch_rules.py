@@ -42,3 +42,13 @@ def test_chunk_lengths(H, most, extra):
                 assert all(100 * cost(c) > 104 * least for c in range(cy + 1, top + 1))
     assert H.cfh_chunk_planes(4, 64, 256, 128, 4) == 1       # four columns: one plane per block
     assert H.cfh_chunk_planes(65536, 64, 768, 32, 2) == 32
+
+
+def test_rows_of_the_corrections_take_eight_blocks(H):
+    """Rows of a multiple of 1024 points are whole blocks, a multiple of the 8 XCDs of
+    them; a block is whole waves and at most 256 threads, a pair of points each."""
+    for nx in [2 ** a for a in range(2, 13)] + [3 * 2 ** a for a in range(1, 11)]:
+        th = H.cfh_correction_threads(nx)
+        assert th % 64 == 0 and 64 <= th <= 256
+        if nx % 1024 == 0:
+            assert nx % (2 * th) == 0 and nx // (2 * th) % 8 == 0
