@@ -171,9 +171,11 @@ struct AdjPtrs {
 // load.  Each XCD takes a contiguous run of every y-chunk's tiles
 // (xcd_slab_block; one run over the whole grid is as fast in FP32 and 12 %
 // slower in FP64).  Bound by its reads: the tiles' halos come to about 1.5 times
-// the fields, mostly from beyond the L2; VALU and LDS are each busy 0.4 of the time.
+// the fields (FP32 on 2048x768x2048 1.6 and 1.9), mostly from beyond the L2; VALU and
+// LDS are each busy 0.4 of the time in FP64.
 // NT: outputs, written once, stored non-temporally for large fields (the
-// two launches of an FP32 adjoint step on 2048x768x2048: 72-74 -> 71.5 ms).
+// two launches of an FP32 adjoint step on 2048x768x2048 in 64 x 8 tiles: 72-74 ->
+// 71.5 ms; 64.5 in the present ones).
 template <typename T, int TX, int TZ, bool HASB, bool ADD, bool NT>
 __global__ void __launch_bounds__(TX * TZ)
 k_rhs_adjoint(AdjPtrs P, T c1, T c2, AdjGeo<T> G, T nu, T s, int cy) {

@@ -426,7 +426,8 @@ void set_partitions(cf_plan* pl, int P, int LB) {
 //              8267 / 8474; 2048x512x1536 2777 / 2761, 34273 / 34511
 //   CF_FP64    128x64x128 7.9 / 13.4, 40 / 46; 512x128x256 (128 MiB of spectrum) 52.5 /
 //              55.1, 247 / 250; 1024x128x512 (513 MiB) 195 / 202, 970 / 967;
-//              1024x192x512 (770 MiB) 299 / 300, 1485 / 1488
+//              1024x192x512 (770 MiB) 299 / 300, 1485 / 1488; with 64 partitions
+//              512x768x128 855 / 850 and, the one above 1 %, 256x768x512 1732 / 1676
 //   CF_FP64 from 1 GiB: neither; whole solves 1024x256x512 1962 / 1968, 512x512x512
 //              1966 / 1969, 1024x384x512 3092 / 3083, 1024x512x512 4039 / 4041,
 //              2048x128x1024 4045 / 4087, 2048x256x1024 8311 / 8260, 2048x384x1024

@@ -85,10 +85,10 @@ struct RkFusedTile {
 
 // At least four waves per SIMD in FP64 (128 VGPRs, five spilled) and six in FP32
 // (three blocks per CU).  The row factors in scalar registers, the walls without
-// branches and the folded averages took the FP64 pass from 360 to 281 VALU and 57
-// to 40 LDS instructions per wave and plane and from 2.18 to 1.88 ms on
+// branches and the folded averages took the FP64 pass from 357 to 281 VALU and 57
+// to 39 LDS instructions per wave and plane and from 2.18 to 1.88 ms on
 // 1024x256x512 (6.44 GB, 3.4 TB/s), and FP32 from 3.78 to 3.07 ms on
-// 1024x384x1024.  VALU issue takes 0.61 of the cycles and LDS 0.48, at a 2.05 GHz
+// 1024x384x1024.  VALU issue takes 0.61 of the cycles and LDS 0.48, at a 2.0 GHz
 // clock; the three waves with outer cells finish last.  Outer cells first, or
 // with a raised priority, are 2-4 % slower.
 // The tile index is remapped (xcd_slab_block over the whole grid) so that each
