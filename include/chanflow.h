@@ -80,7 +80,9 @@ typedef struct {
   int drop_parts;     /* G: the dropped reduced system is an outer PDD of G partitions, each a
                          group of n_parts/G consecutive partitions solved exactly inside
                          (Section 2.2 with G partitions); the corner terms of the G-level
-                         Eq. (21) are what drop_tol bounds.  Must divide n_parts.  0 =
+                         Eq. (21) are what drop_tol bounds.  Must divide n_parts (with
+                         n_parts = 0 a count that it divides is taken, if the automatic or
+                         the even partitioning of ny has one).  0 =
                          automatic: 4 when 4 divides n_parts, else n_parts */
 } cf_options;
 
@@ -100,8 +102,8 @@ typedef struct {
    fastest and sets the drop threshold for its P (each candidate's accuracy
    follows drop_tol, so the choice affects speed, not the error bound).  Needs
    n_parts = 0, lines_per_block = 0 and the partitioned solve (no CF_PLAN_Y_DCT);
-   the timings are read back with cf_plan_tuning.  Takes tens of milliseconds
-   on large grids. */
+   the timings are read back with cf_plan_tuning.  Takes from some
+   milliseconds to about a second on the largest grids. */
 enum { CF_PLAN_STEP = 1, CF_PLAN_ADJOINT = 2, CF_PLAN_Y_DCT = 4, CF_PLAN_TUNE_PARTS = 8 };
 
 typedef struct {
